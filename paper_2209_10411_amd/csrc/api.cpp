@@ -1478,7 +1478,7 @@ struct lbm_batch {
     int map_off[BK_N] = {}, map_n[BK_N] = {};
     std::vector<CaseArgs> h_args;
     std::vector<Params> h_p;  // each system's constants when the tables were written (byte copies)
-    bool any_rigid = false, any_warm = false;
+    bool any_rigid = false, any_warm = false, link_q_one = false;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<uintptr_t> graph_key;
@@ -1515,14 +1515,14 @@ BulkCase bulk_case(const lbm_ctx *c, int twl, int bw, int first_block) {
 // Block ranges of a system in the batched boundary launches (the one-system
 // launch sizes; systems without bodies take no blocks but the force
 // reduction's, whose block 0 clears the step counters).
-void case_blocks(const lbm_ctx *c, int nb[BK_N]) {
+void case_blocks(const lbm_ctx *c, bool one, int nb[BK_N]) {
     const Params &p = c->p;
     const bool bodies = p.np > 0;
     nb[BK_LINKS] = bodies ? link_grid(p) : 0;
     nb[BK_REDUCE] = std::max(p.np, 1);
     nb[BK_RIGID] = bodies && p.contact ? 1 : 0;
     nb[BK_REGION] = bodies ? p.region_blocks : 0;
-    nb[BK_LINKQ] = bodies ? link_q_grid(p) : 0;
+    nb[BK_LINKQ] = bodies ? link_q_grid(p, one) : 0;
 }
 
 // Largest block ranges of a system (list grids at full capacity).
@@ -1530,7 +1530,7 @@ long long case_blocks_cap(const Params &p) {
     if (p.np <= 0) return 1;
     Params q = p;
     q.est_links = 0;  // 0: sized for the capacity
-    return (long long)link_grid(q) + p.np + 1 + p.region_blocks + link_q_grid(q);
+    return (long long)link_grid(q) + p.np + 1 + p.region_blocks + link_q_grid(q, false);
 }
 
 // Argument block of system c, k steps after its current state (buffer
@@ -1581,8 +1581,11 @@ lbm_status write_table(lbm_batch *b) {
     std::vector<int> nb((size_t)b->n * BK_N);
     int tot[BK_N] = {};
     b->any_rigid = b->any_warm = false;
+    long long links = 0;  // the solver's form follows the links of the whole launch
+    for (int i = 0; i < b->n; ++i) links += link_q_expected(b->cs[i]->p);
+    b->link_q_one = link_q_one(links);
     for (int i = 0; i < b->n; ++i) {
-        case_blocks(b->cs[i], &nb[(size_t)i * BK_N]);
+        case_blocks(b->cs[i], b->link_q_one, &nb[(size_t)i * BK_N]);
         for (int k = 0; k < BK_N; ++k) tot[k] += nb[(size_t)i * BK_N + k];
         b->any_rigid = b->any_rigid || nb[(size_t)i * BK_N + BK_RIGID] > 0;
         b->any_warm = b->any_warm || b->cs[i]->warm != nullptr;
@@ -1684,7 +1687,8 @@ lbm_status enqueue_batch_step(lbm_batch *b) {
     run(OP_CLASSIFY, BK_REGION);
     HIPCHK(hipEventRecord(b->ev_flags[0], ax));
     run(OP_EMIT, BK_REGION);
-    run(b->any_warm ? OP_LINKQ_WARM : OP_LINKQ, BK_LINKQ);
+    run(b->any_warm ? (b->link_q_one ? OP_LINKQ_WARM_ONE : OP_LINKQ_WARM) : b->link_q_one ? OP_LINKQ_ONE : OP_LINKQ,
+        BK_LINKQ);
     launch_bulk_batch(b->storage, b->bw, b->d_cases, b->d_blk, b->nblocks, b->phase & 1, b->main);
     HIPCHK(hipStreamWaitEvent(b->main, b->ev_flags[0], 0));
     for (int i = 0; i < b->n; ++i) {

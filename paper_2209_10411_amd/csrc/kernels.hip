@@ -19,8 +19,8 @@
 //   k_link_emit_*    cut-link list of the new geometry (masks and counts from
 //                    the classification; a fixed grid visits the tiles with
 //                    links)
-//   k_link_q         link fractions q, eight lanes per link, by a safeguarded
-//                    Newton iteration in FP64
+//   k_link_q         link fractions q, eight lanes or one per link, by a
+//                    safeguarded Newton iteration in FP64
 // Populations are deviations f_i - w_i rho0 in FP32, FP16 or BF16 storage;
 // collisions run in FP32, everything geometric or mechanical in FP64.
 #include <hip/hip_ext.h>
@@ -35,6 +35,18 @@
 #include "stream_collide.h"
 
 namespace mdl {
+
+// D3Q19 tables indexable by a runtime lane number.
+__constant__ int c_ex[Q] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0};
+__constant__ int c_ey[Q] = {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1};
+__constant__ int c_ez[Q] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1};
+__constant__ int c_opp[Q] = {0, 2, 1, 4, 3, 6, 5, 8, 7, 10, 9, 12, 11, 14, 13, 16, 15, 18, 17};
+__constant__ float c_w[Q] = {1.f / 3, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18,
+                             1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36,
+                             1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36};
+__constant__ double c_wd[Q] = {1.0 / 3,  1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
+                               1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
+                               1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
 
 __device__ __forceinline__ void node_xyz(const Params &p, long long n, int &x, int &y, int &z) {
     if (p.N <= 0xffffffffLL) {  // 32-bit quotients (far shorter than 64-bit division)
@@ -203,6 +215,15 @@ __device__ __forceinline__ bool metaball_ge1(const Params &p, const CPs &P, cons
     return metaball_ge(p, P, x, 1.0, Cf);
 }
 
+// Where the FP32 sum C at the point r (relative to the anchor) decides: 1 for
+// C >= L, -1 for C < L, 0 within its bound of L (the bound: metaball_ge32).
+__device__ __forceinline__ int ge32_side(const CPs &P, float rx, float ry, float rz, float C, double L) {
+    const float ax = fabsf(rx) + fabsf(ry) + fabsf(rz);
+    const double rel = 1.5 * 5.9604644775390625e-8 * (2.03 * ((double)ax + (double)P.bp) + 9.5 + P.n);
+    const double Cd = (double)C;
+    return Cd * (1.0 - rel) > L * (1.0 + 1e-12) ? 1 : Cd * (1.0 + rel) < L * (1.0 - 1e-12) ? -1 : 0;
+}
+
 // Whether C(x) >= L, decided first in FP32 where the FP32 sum is certain to
 // fall on the same side as the exact one, else by metaball_ge.  FP32 form:
 // r = x - X and the points' p - X rounded to FP32 (X the anchor), d = r - p,
@@ -243,11 +264,9 @@ __device__ __forceinline__ bool metaball_ge32(const Params &p, const CPs &P, con
             }
         }
         if (rmin >= 1.f) {
-            const float ax = fabsf(rx) + fabsf(ry) + fabsf(rz);
-            const double rel = 1.5 * 5.9604644775390625e-8 * (2.03 * ((double)ax + (double)P.bp) + 9.5 + P.n);
-            const double Cd = (double)C;
-            if (Cd * (1.0 - rel) > L * (1.0 + 1e-12)) { Cf = Cd; return true; }
-            if (Cd * (1.0 + rel) < L * (1.0 - 1e-12)) { Cf = Cd; return false; }
+            const int side = ge32_side(P, rx, ry, rz, C, L);
+            Cf = (double)C;
+            if (side) return side > 0;
         }
     }
     return metaball_ge(p, P, x, L, Cf);
@@ -281,14 +300,29 @@ __device__ __forceinline__ double wave_sum_fixed(double v) {
     return v + __shfl_xor(v, 32);
 }
 
-// C and dC/ds at x_f - s e_i for one link held by an aligned group of eight
-// lanes: lane j sums control points j, j + 8, ... and the group adds its
-// partial sums by a butterfly, which leaves the same bits in every lane.
-// These values steer the Newton iteration and judge its residual to 1e-15 of
-// the level, so they are formed with fused multiply-adds and refined
-// reciprocals.
-__device__ void metaball_ds8(const Params &p, const CPs &P, const double xf[3], const double e[3], double s,
-                             double &C, double &dC) {
+// One control point's share of C and dC/ds at distance d from it along a link
+// of direction e.  These values steer the Newton iteration and judge its
+// residual to 1e-15 of the level, so they are formed with fused
+// multiply-adds and refined reciprocals.
+__device__ __forceinline__ void ds_term(const CPs &P, int i, const double d[3], const double e[3], double &c,
+                                        double &g) {
+#pragma clang fp contract(off)
+    const double r2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
+    const double inv = rcp_refined(r2);
+    const double kr = P.k[i] * inv;
+    const bool on_point = r2 == 0.0;
+    c = on_point ? __builtin_inf() : fma(P.k[i], inv, c);
+    g = on_point ? g : fma(2.0 * kr * inv, fma(d[0], e[0], fma(d[1], e[1], d[2] * e[2])), g);
+}
+
+// C and dC/ds at x_f - s e_i for one link held by G lanes.  G = 8 (an aligned
+// group, all active): lane j sums control points j, j + 8, ... and the group
+// adds its partial sums by a butterfly, which leaves the same bits in every
+// lane.  G = 1: one lane forms the same eight partial sums and adds them in
+// the same tree, so both forms return the same bits.
+template <int G>
+__device__ __forceinline__ void metaball_ds(const Params &p, const CPs &P, const double xf[3], const double e[3],
+                                            double s, double &C, double &dC) {
     double xs[3] = {xf[0] - s * e[0], xf[1] - s * e[1], xf[2] - s * e[2]};
     bool img = P.img;
     if (img) {
@@ -305,53 +339,172 @@ __device__ void metaball_ds8(const Params &p, const CPs &P, const double xf[3], 
             img = false;
         }
     }
-    double c = 0.0, g = 0.0;
-    for (int i = threadIdx.x & 7; i < P.n; i += 8) {
-        double d[3] = {xs[0] - P.x[i][0], xs[1] - P.x[i][1], xs[2] - P.x[i][2]};
-        if (img) min_image(p, d);
-        const double r2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
-        if (r2 == 0.0) {
-            c = __builtin_inf();
-            continue;
+    if (G == 1 && !img) {
+        double c[8] = {0, 0, 0, 0, 0, 0, 0, 0}, g[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        auto four = [&](int i0, double *cu, double *gu) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double d[3] = {xs[0] - P.x[i0 + u][0], xs[1] - P.x[i0 + u][1], xs[2] - P.x[i0 + u][2]};
+                ds_term(P, i0 + u, d, e, cu[u], gu[u]);
+            }
+            __builtin_amdgcn_sched_barrier(0);  // four points in flight: more would spill
+        };
+#pragma unroll 1
+        for (int i0 = 0; i0 < P.n; i0 += 8) {
+            four(i0, c, g);
+            if (i0 + 4 < P.n) four(i0 + 4, c + 4, g + 4);
         }
-        const double inv = rcp_refined(r2);
-        const double kr = P.k[i] * inv;
-        c += kr;
-        g = fma(2.0 * kr * inv, fma(d[0], e[0], fma(d[1], e[1], d[2] * e[2])), g);
+        C = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+        dC = ((g[0] + g[1]) + (g[2] + g[3])) + ((g[4] + g[5]) + (g[6] + g[7]));
+        return;
     }
-    C = group8_sum(c);
-    dC = group8_sum(g);
+    // one partial sum: lane j's, or (an image per point: a body about as large
+    // as half the box) each of the eight in turn
+    auto partial = [&](int j, double &c, double &g) {
+        c = g = 0.0;
+        for (int i = j; i < P.n; i += 8) {
+            double d[3] = {xs[0] - P.x[i][0], xs[1] - P.x[i][1], xs[2] - P.x[i][2]};
+            if (img) min_image(p, d);
+            ds_term(P, i, d, e, c, g);
+        }
+    };
+    double c, g;
+    if (G == 8) {
+        partial(threadIdx.x & 7, c, g);
+        C = group8_sum(c);
+        dC = group8_sum(g);
+        return;
+    }
+    double c1 = 0, g1 = 0, c2 = 0, g2 = 0, c4 = 0, g4 = 0;  // the tree's open branches
+#pragma unroll 1
+    for (int j = 0; j < 8; ++j) {
+        partial(j, c, g);
+        if (!(j & 1)) { c1 = c; g1 = g; continue; }
+        c = c1 + c; g = g1 + g;
+        if (!(j & 2)) { c2 = c; g2 = g; continue; }
+        c = c2 + c; g = g2 + g;
+        if (!(j & 4)) { c4 = c; g4 = g; continue; }
+        C = c4 + c;
+        dC = g4 + g;
+    }
+}
+
+// Bracket of a link fraction: the first of the samples s = (j + 1)/8, j =
+// 0..7, with C >= L, decided exactly as the flagging decides (metaball_ge32);
+// -1: none.  Chi, Clo: C there and at the sample before.  Eight lanes, one
+// sample each:
+__device__ __forceinline__ int link_bracket8(const Params &p, const CPs &P, const double xf[3], const double e[3],
+                                             double &Chi, double &Clo) {
+    const int lane = threadIdx.x & 63, j = lane & 7, base = lane & 56;
+    const double sj = (double)(j + 1) / 8.0;
+    const double xj[3] = {xf[0] - sj * e[0], xf[1] - sj * e[1], xf[2] - sj * e[2]};
+    double Cj;
+    const bool inj = metaball_ge32(p, P, xj, P.level, Cj);
+    const unsigned grp = (unsigned)((__ballot(inj) >> base) & 0xffull);
+    const int k0 = grp ? __ffs(grp) - 1 : 7;
+    Chi = __shfl(Cj, base + k0);
+    Clo = __shfl(Cj, base + (k0 > 0 ? k0 - 1 : 0));
+    return grp ? k0 : -1;
+}
+
+// One lane, the FP32 sums of metaball_ge32 for all eight samples in one pass
+// over the points; samples that its bound leaves open are decided in FP64 as
+// far as the first one inside.
+__device__ __forceinline__ int link_bracket1(const Params &p, const CPs &P, const double xf[3], const double e[3],
+                                             double &Chi, double &Clo) {
+    constexpr int NS = 8;
+    const double L = P.level;
+    float rx[NS], ry[NS], rz[NS], Cs[NS], rmin[NS];
+    // whole periods from x_f - X to its minimum image; a sample with another
+    // shift lies within one node of half a box and is far below
+    double shift[3] = {0.0, 0.0, 0.0}, room[3] = {0.0, 0.0, 0.0};
+    unsigned far = 0u;  // samples whose differences could reach half a periodic box
+    if (P.img) {
+        const double d[3] = {xf[0] - P.anc[0], xf[1] - P.anc[1], xf[2] - P.anc[2]};
+        double r[3] = {d[0], d[1], d[2]};
+        min_image(p, r);
+        const double Lb[3] = {(double)p.nx, (double)p.ny, (double)p.nz};
+        for (int a = 0; a < 3; ++a) {
+            shift[a] = rint(d[a] - r[a]);
+            room[a] = (p.periodic >> a) & 1u ? 0.5 * Lb[a] - 1.0 : __builtin_inf();
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const double sj = (double)(j + 1) / 8.0;
+        const double r[3] = {xf[0] - sj * e[0] - P.anc[0] - shift[0], xf[1] - sj * e[1] - P.anc[1] - shift[1],
+                             xf[2] - sj * e[2] - P.anc[2] - shift[2]};
+        if (P.img)
+            for (int a = 0; a < 3; ++a)
+                if (!(fabs(r[a]) + (double)P.bp < room[a])) far |= 1u << j;
+        rx[j] = (float)r[0]; ry[j] = (float)r[1]; rz[j] = (float)r[2];
+        Cs[j] = 0.f;
+        rmin[j] = 1.f;
+    }
+    for (int k = 0; k < P.n; ++k) {
+        const float4 c = P.f[k];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const float dx = rx[j] - c.x, dy = ry[j] - c.y, dz = rz[j] - c.z;
+            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            rmin[j] = fminf(rmin[j], r2);
+            Cs[j] = fmaf(c.w, __builtin_amdgcn_rcpf(r2), Cs[j]);
+        }
+    }
+    unsigned in = 0u, open = 0u;  // samples certainly inside, and those the bound leaves open
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int side = !((far >> j) & 1u) && rmin[j] >= 1.f ? ge32_side(P, rx[j], ry[j], rz[j], Cs[j], L) : 0;
+        if (side > 0) in |= 1u << j;
+        if (side == 0) open |= 1u << j;
+    }
+    int k0 = -1, jd = -1, jh = -1;
+    double Cd = 0.0;  // the FP64 value of the open sample jd (outside) or jh (inside)
+    for (unsigned todo = in | open; todo && k0 < 0; todo &= todo - 1u) {
+        const int j = __ffs(todo) - 1;
+        bool hit = (in >> j) & 1u;
+        if (!hit) {
+            const double sj = (double)(j + 1) / 8.0;
+            const double xj[3] = {xf[0] - sj * e[0], xf[1] - sj * e[1], xf[2] - sj * e[2]};
+            double Cf;
+            hit = metaball_ge(p, P, xj, L, Cf);
+            if (hit) { jh = j; Chi = Cf; }
+            else { jd = j; Cd = Cf; }
+        }
+        if (hit) k0 = j;
+    }
+    Clo = 0.0;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        if (j == k0 && jh != j) Chi = (double)Cs[j];
+        if (j == k0 - 1) Clo = jd == j ? Cd : (double)Cs[j];
+    }
+    return k0;
 }
 
 // Link fraction q (sec. 2.3.2): the first root of C(x_f - s e_i) = L on
 // (0,1] (L = P.level: 1, or c_0 for the sphero-metaball's inner body), for
-// one link by an aligned group of eight lanes (all active).
-// Bracket: lane j decides C >= 1 at s = (j + 1)/8 exactly as the flagging
-// does (metaball_ge1), and the first of the eight sub-interval ends with C >= 1 closes
-// the bracket (none: q = 1).  Then a safeguarded Newton iteration
+// one link by G lanes: G = 8, an aligned group (all active), or G = 1.
+// The bracket of eight samples (none inside: q = 1), then a safeguarded
+// Newton iteration
 // (rtsafe-style: a Newton step that leaves the bracket or does not halve the
 // step falls back to bisection) to |step| < 1e-13 or |C - 1| < 1e-15,
 // started at the guess when it lies inside the bracket, else by regula
 // falsi on the bracket ends, for at most it_max evaluations (conv:
-// converged).  Every lane returns the same
+// converged).  Every lane of a group returns the same
 // q and resid = C - 1 at the last evaluation; the return value is the
 // number of evaluations of the iteration.
-__device__ int link_fraction8(const Params &p, const CPs &P, int x, int y, int z, int i, double guess,
-                              int it_max, double &q, double &resid, bool &conv) {
-    const int lane = threadIdx.x & 63, j = lane & 7, base = lane & 56;
+template <int G>
+__device__ __forceinline__ int link_fraction(const Params &p, const CPs &P, int x, int y, int z, int i, double guess,
+                                             int it_max, double &q, double &resid, bool &conv) {
     const double xf[3] = {(double)x, (double)y, (double)z};
-    const double e[3] = {(double)EX[i], (double)EY[i], (double)EZ[i]};
-    const double sj = (double)(j + 1) / 8.0;
-    const double xj[3] = {xf[0] - sj * e[0], xf[1] - sj * e[1], xf[2] - sj * e[2]};
-    double Cj;
+    const double e[3] = {(double)c_ex[i], (double)c_ey[i], (double)c_ez[i]};
     const double L = P.level;
-    const bool inj = metaball_ge32(p, P, xj, L, Cj);
-    const unsigned grp = (unsigned)((__ballot(inj) >> base) & 0xffull);
-    const int k0 = grp ? __ffs(grp) - 1 : 7;
-    const double Chi = __shfl(Cj, base + k0), Clo = __shfl(Cj, base + (k0 > 0 ? k0 - 1 : 0));
+    double Chi = 0.0, Clo = 0.0;
+    const int k0 = G == 8 ? link_bracket8(p, P, xf, e, Chi, Clo) : link_bracket1(p, P, xf, e, Chi, Clo);
     resid = 0.0;
     conv = true;
-    if (!grp) {
+    if (k0 < 0) {
         q = 1.0;
         return 0;
     }
@@ -367,7 +520,7 @@ __device__ int link_fraction8(const Params &p, const CPs &P, int x, int y, int z
     conv = false;
     while (it < it_max) {
         double C, dC;
-        metaball_ds8(p, P, xf, e, s, C, dC);
+        metaball_ds<G>(p, P, xf, e, s, C, dC);
         ++it;
         const double g = C - L;
         resid = g;
@@ -376,7 +529,7 @@ __device__ int link_fraction8(const Params &p, const CPs &P, int x, int y, int z
             break;
         }
         if (g >= 0.0) hi = s; else lo = s;
-        const double sn = s - g * rcp_refined(dC);  // a zero or tiny slope leaves the bracket: bisection
+        const double sn = fma(-g, rcp_refined(dC), s);  // a zero or tiny slope leaves the bracket: bisection
         if (!(dC != 0.0) || !(sn > lo && sn < hi) || fabs(2.0 * g) > fabs(dxold * dC)) {
             dxold = dx;
             dx = 0.5 * (hi - lo);
@@ -426,18 +579,6 @@ __device__ __forceinline__ void cross3(const double a[3], const double b[3], dou
     o[2] = a[0] * b[1] - a[1] * b[0];
 }
 
-
-// D3Q19 tables indexable by a runtime lane number.
-__constant__ int c_ex[Q] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0};
-__constant__ int c_ey[Q] = {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1};
-__constant__ int c_ez[Q] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1};
-__constant__ int c_opp[Q] = {0, 2, 1, 4, 3, 6, 5, 8, 7, 10, 9, 12, 11, 14, 13, 16, 15, 18, 17};
-__constant__ float c_w[Q] = {1.f / 3, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18, 1.f / 18,
-                             1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36,
-                             1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36, 1.f / 36};
-__constant__ double c_wd[Q] = {1.0 / 3,  1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
-                               1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
-                               1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
 
 // Second-order equilibrium of a runtime direction in FP64.
 __device__ __forceinline__ double feq64d(int i, double rho, const double u[3]) {
@@ -2061,14 +2202,23 @@ __global__ __launch_bounds__(BLK) void k_link_emit_tiles(Params p, RegionMap rm,
         });
 }
 
-// Link build, third pass: the link fractions of the whole list, eight lanes
-// per link (32 links per block, blocks stride over the list), each wave
-// staging one body's control points at a time in its LDS slot (a small slot
-// per wave leaves room for several blocks per CU beside the stream-collide).
-// With WARM the Newton iteration starts at the network's guess that the first
-// pass (k_link_guess) left in l_q; a warm-started iteration that has not
-// converged in NR_WARM_MAX evaluations is replaced by the plain one.  Per block: iteration histogram and largest
-// final |C - 1|, added to the statistics.
+// Link build, third pass: the link fractions of the whole list, G lanes per
+// link (256 / G links per block and round, blocks stride over the list), each
+// wave staging one body's control points at a time in its LDS slot (a small
+// slot per wave leaves room for several blocks per CU beside the
+// stream-collide).  With WARM the Newton iteration starts at the network's
+// guess that the first pass (k_link_guess) left in l_q; a warm-started
+// iteration that has not converged in NR_WARM_MAX evaluations is replaced by
+// the plain one.  Per block: iteration histogram and largest final |C - 1|,
+// added to the statistics.
+// G = 8 shortens the chain of one link (the samples side by side, the points
+// shared out), G = 1 does the least work per link: the step control, the
+// butterflies and the frame of a link are not repeated in eight lanes.  Both
+// are bound by vector issue once they fill the chip.  1.45 M links (200 bodies
+// in 256^3): G = 8 354 us alone and 577 us beside the stream-collide, G = 1
+// 188 and 270 us; 24 systems, 200 k links in one launch, 204 -> 76 us; 900
+// links: G = 8 14 us, G = 1 21 us.  The lines cross where G = 8's waves (one
+// per eight links) begin to queue.
 constexpr int NR_WARM_MAX = 30, NR_MAX = 100;
 // Warm start, first pass: the network's q for every link of the list, written
 // to l_q as the solver's start (one wave per 32 links, the wave inference of
@@ -2140,7 +2290,7 @@ __global__ __launch_bounds__(256) void k_link_guess(Params p, const DevParticle 
 
 // Second pass (or the plain solve): WARM takes the start from l_q; a system
 // without weights (wts NULL) takes the plain iteration in either form.
-template <bool WARM>
+template <bool WARM, int G>
 __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *__restrict__ P,
                                             const uint32_t *__restrict__ l_node,
                                             const uint32_t *__restrict__ l_do, double *__restrict__ l_q,
@@ -2150,30 +2300,32 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
     __shared__ int sh[256];
     __shared__ unsigned hist[NR_HIST];
     __shared__ unsigned rmax;
-    const int t = threadIdx.x, g = t >> 3, j = t & 7, w = t >> 6;
+    constexpr int LPB = 256 / G;  // links per block and round
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63, g = t / G;
+    const bool lead = t % G == 0;  // the lane that reports its group's link
     const bool warm = WARM && wts != nullptr;  // block-uniform
     for (int b = t; b < NR_HIST; b += 256) hist[b] = 0u;
     if (t == 0) rmax = 0u;
     __syncthreads();
-    // From here each wave runs its own eight groups through the rounds: the
-    // wave's slot cps[w] is written and read only by its own lanes, so the
-    // rounds need no block barrier (a wave does not wait for the slowest
-    // link of the other three).
+    // From here each wave runs its own links through the rounds: the wave's
+    // slot cps[w] is written and read only by its own lanes, so the rounds
+    // need no block barrier (a wave does not wait for the slowest link of the
+    // other three).
     const int nl = min(cnt->n_links, p.link_cap);
     int it_sum = 0, links = 0;
     // the next round's link record is loaded while this round solves
     uint32_t nx_node = 0, nx_do = 0;
-    if (bid * 32 + g < nl) {
-        nx_node = l_node[bid * 32 + g];
-        nx_do = l_do[bid * 32 + g];
+    if (bid * LPB + g < nl) {
+        nx_node = l_node[bid * LPB + g];
+        nx_do = l_do[bid * LPB + g];
     }
-    for (int l0 = bid * 32; l0 < nl; l0 += nblk * 32) {  // block-uniform trip count
+    for (int l0 = bid * LPB; l0 < nl; l0 += nblk * LPB) {  // block-uniform trip count
         const int l = l0 + g;
         const bool ok0 = l < nl;
         const uint32_t cur_node = nx_node, cur_do = nx_do;
-        if (l + nblk * 32 < nl) {
-            nx_node = l_node[l + nblk * 32];
-            nx_do = l_do[l + nblk * 32];
+        if (l + nblk * LPB < nl) {
+            nx_node = l_node[l + nblk * LPB];
+            nx_do = l_do[l + nblk * LPB];
         }
         int pid = 0, i = 1;
         long long n = 0;
@@ -2182,7 +2334,7 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
             i = (int)(cur_do & 31u);
             pid = (int)(cur_do >> 8);
             if (n >= p.N || pid >= p.np || i < 1 || i >= Q) {  // never expected: report, solve nothing
-                if (j == 0) atomicOr(&cnt->err, ERR_BAD_INDEX);
+                if (lead) atomicOr(&cnt->err, ERR_BAD_INDEX);
             }
         }
         const bool ok = ok0 && n < p.N && pid < p.np && i >= 1 && i < Q;
@@ -2190,12 +2342,14 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
         if (ok) node_xyz(p, n, x, y, z);
         double guess = -1.0;
         if (warm && ok) guess = l_q[l];  // the first pass's network output
-        // The wave's links come body by body from the list, so its eight
-        // groups nearly always share one body: the wave stages one body's
-        // points at a time into its slot (lane k point k, padded to a
-        // multiple of 4 with weight 0) and the groups of that body solve;
-        // a wave across a body boundary takes a second turn.
+        // The wave's links come body by body from the list, so they nearly
+        // always share one body: the wave stages one body's points at a time
+        // into its slot (lane k point k, padded to a multiple of 4 with
+        // weight 0) and the groups of that body solve; a wave across a body
+        // boundary takes a second turn.
         bool pending = ok;
+        int its = -1;  // evaluations of this lane's link (-1: none solved)
+        double resid = 0.0;
         for (;;) {  // wave-uniform
             const unsigned long long pm = __ballot(pending);
             if (!pm) break;
@@ -2206,7 +2360,7 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
             // centroid, weights s^2 k) at the level c_0 = s^2
             const bool inner = p.link_c0 && p.c_rs > 0.0;
             const double sc = inner ? 1.0 - p.c_rs * B.rsk : 1.0;
-            const int k = t & 63;
+            const int k = lane;
             float bmax = 0.f;
             if (k < n4) {
                 const int src = k < B.n_cp ? k : 0;
@@ -2225,22 +2379,44 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
             wave_sync();  // the slot is staged
             if (pending && pid == bpid) {  // group-uniform
                 pending = false;
-                double q, resid;
+                double q;
                 bool conv;
-                int its = link_fraction8(p, cps[w], x, y, z, i, guess, warm ? NR_WARM_MAX : NR_MAX, q, resid,
-                                         conv);
-                if (warm && !conv) {
-                    its += link_fraction8(p, cps[w], x, y, z, i, -1.0, NR_MAX, q, resid, conv);
+                if (WARM) {
+                    its = 0;
+                    for (int turn = warm ? 0 : 1; turn < 2; ++turn) {  // turn 0: from the guess
+                        its += link_fraction<G>(p, cps[w], x, y, z, i, turn == 0 ? guess : -1.0,
+                                                turn == 0 ? NR_WARM_MAX : NR_MAX, q, resid, conv);
+                        if (conv) break;
+                    }
+                } else {
+                    its = link_fraction<G>(p, cps[w], x, y, z, i, guess, NR_MAX, q, resid, conv);
                 }
-                if (j == 0) {
+                if (lead) {
                     l_q[l] = q;
                     it_sum += its;
                     ++links;
-                    atomicAdd(&hist[min(its, NR_HIST - 1)], 1u);
-                    atomicMax(&rmax, __float_as_uint((float)fabs(resid)));
                 }
             }
             wave_sync();  // the slot is restaged next
+        }
+        if (G == 8) {
+            if (lead && its >= 0) {
+                atomicAdd(&hist[min(its, NR_HIST - 1)], 1u);
+                atomicMax(&rmax, __float_as_uint((float)fabs(resid)));
+            }
+        } else {
+            // one LDS atomic per distinct count in the wave: its lanes nearly
+            // all take the same three or four
+            const float rw = wave_fmax(its >= 0 ? (float)fabs(resid) : 0.f);
+            if (lane == 0) atomicMax(&rmax, __float_as_uint(rw));
+            const int bin = min(its, NR_HIST - 1);
+            unsigned long long left = __ballot(its >= 0);
+            while (left) {  // wave-uniform
+                const int v = __shfl(bin, __ffsll((long long)left) - 1);
+                const unsigned long long same = __ballot(bin == v) & left;
+                if (lane == 0) atomicAdd(&hist[v], (unsigned)__popcll(same));
+                left &= ~same;
+            }
         }
     }
     __syncthreads();
@@ -2257,12 +2433,12 @@ __device__ __forceinline__ void link_q_body(const Params &p, const DevParticle *
         if (hist[b]) nrs.hist[bid * NR_HIST + b] += hist[b];
 }
 
-template <bool WARM>
+template <bool WARM, int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_link_q(Params p, const DevParticle *__restrict__ P,
                                                 const uint32_t *__restrict__ l_node,
                                                 const uint32_t *__restrict__ l_do, double *__restrict__ l_q,
                                                 Counters *cnt, NrStats nrs, const _Float16 *__restrict__ wts) {
-    link_q_body<WARM>(p, P, l_node, l_do, l_q, cnt, nrs, wts, blockIdx.x, gridDim.x);
+    link_q_body<WARM, G>(p, P, l_node, l_do, l_q, cnt, nrs, wts, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------- batched boundary kernels
@@ -2317,10 +2493,10 @@ __global__ __launch_bounds__(256) void k_link_guess_batch(const CaseArgs *__rest
                     (int)blockIdx.x - a.first[BK_LINKQ], a.nblk[BK_LINKQ]);
 }
 
-template <bool WARM>
-__global__ __launch_bounds__(256) void k_link_q_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
+template <bool WARM, int G>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_link_q_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
     const CaseArgs &a = cs[map[blockIdx.x]];
-    link_q_body<WARM>(a.p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, a.warm, (int)blockIdx.x - a.first[BK_LINKQ],
+    link_q_body<WARM, G>(a.p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, a.warm, (int)blockIdx.x - a.first[BK_LINKQ],
                       a.nblk[BK_LINKQ]);
 }
 
@@ -2330,7 +2506,14 @@ static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b)
 // list kernels stride over their lists; size their grids for the expected lengths
 static int expected_links(const Params &p) { return p.est_links > 0 ? min(p.est_links, p.link_cap) : p.link_cap; }
 int link_grid(const Params &p) { return max(1, min(cdiv(expected_links(p), 256), 2048)); }
-int link_q_grid(const Params &p) { return max(1, min(cdiv(expected_links(p), 32), NR_BLOCKS)); }
+// G = 8 below LINKQ_ONE links: 4096 waves of eight links are four per SIMD, as
+// many as are resident; beyond, they run in rounds and G = 1 is the shorter.
+constexpr int LINKQ_ONE = 32768;
+bool link_q_one(long long links) { return links >= LINKQ_ONE; }
+int link_q_grid(const Params &p, bool one) {
+    return max(1, min(cdiv(expected_links(p), one ? 256 : 32), NR_BLOCKS));
+}
+long long link_q_expected(const Params &p) { return p.np > 0 ? expected_links(p) : 0; }
 constexpr int LINK_GUESS_BLOCKS = 1024;  // 4096 waves, each loads the network once
 
 // LDS reserved (and not used) by each stream-collide block, so that at most
@@ -2437,13 +2620,18 @@ static void launch_step_kernels_t(const StepArgs &a) {
             k_link_emit_tiles<<<region_grid(p), BLK, 0, a.stream>>>(p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats,
                                                                      a.part_first_blk, a.l_off, a.l_node, a.l_do,
                                                                      a.cnt);
-            const int qg = link_q_grid(p);
+            const bool one = link_q_one(link_q_expected(p));
+            const int qg = link_q_grid(p, one);
+            auto solve = [&](auto kernel, const _Float16 *w) {
+                kernel<<<qg, 256, 0, a.stream>>>(p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, w);
+            };
             if (a.warm) {  // the network's guesses over the list, then the solve
                 k_link_guess<<<min(cdiv(expected_links(p), 128), LINK_GUESS_BLOCKS), 256, 0, a.stream>>>(
                     p, a.P, a.l_node, a.l_do, a.cnt, a.warm, a.mlp_body, a.l_q);
-                k_link_q<true><<<qg, 256, 0, a.stream>>>(p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, a.warm);
-            } else
-                k_link_q<false><<<qg, 256, 0, a.stream>>>(p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, nullptr);
+                solve(one ? k_link_q<true, 1> : k_link_q<true, 8>, a.warm);
+            } else {
+                solve(one ? k_link_q<false, 1> : k_link_q<false, 8>, nullptr);
+            }
         }
     } else if (a.phase == PHASE_INIT_STATE) {
         k_init_state<S><<<2048, 256, 0, a.stream>>>(p, A, a.own_old);
@@ -2490,10 +2678,15 @@ static void launch_case_batch_t(BatchOp op, const CaseArgs *cs, const int *map, 
         case OP_MARK: k_region_mark_batch<<<nblocks, BLK, 0, s>>>(cs, map); break;
         case OP_CLASSIFY: k_region_classify_batch<S><<<nblocks, BLK, 0, s>>>(cs, map); break;
         case OP_EMIT: k_link_emit_batch<<<nblocks, BLK, 0, s>>>(cs, map); break;
-        case OP_LINKQ: k_link_q_batch<false><<<nblocks, 256, 0, s>>>(cs, map); break;
+        case OP_LINKQ: k_link_q_batch<false, 8><<<nblocks, 256, 0, s>>>(cs, map); break;
+        case OP_LINKQ_ONE: k_link_q_batch<false, 1><<<nblocks, 256, 0, s>>>(cs, map); break;
         case OP_LINKQ_WARM:  // guesses of the systems with a network, then every solve
             k_link_guess_batch<<<nblocks, 256, 0, s>>>(cs, map);
-            k_link_q_batch<true><<<nblocks, 256, 0, s>>>(cs, map);
+            k_link_q_batch<true, 8><<<nblocks, 256, 0, s>>>(cs, map);
+            break;
+        case OP_LINKQ_WARM_ONE:
+            k_link_guess_batch<<<nblocks, 256, 0, s>>>(cs, map);
+            k_link_q_batch<true, 1><<<nblocks, 256, 0, s>>>(cs, map);
             break;
     }
 }

@@ -63,11 +63,16 @@ void launch_refresh_pose(const Params &p, DevParticle *P, int fresh, hipStream_t
 
 // Batched boundary kernels of an ensemble: one launch of a kind for every
 // system (cs: the systems' argument blocks, map: block -> system).
-enum BatchOp { OP_LINKS, OP_REDUCE, OP_RIGID, OP_MARK, OP_CLASSIFY, OP_EMIT, OP_LINKQ, OP_LINKQ_WARM };
+enum BatchOp { OP_LINKS, OP_REDUCE, OP_RIGID, OP_MARK, OP_CLASSIFY, OP_EMIT, OP_LINKQ, OP_LINKQ_ONE, OP_LINKQ_WARM,
+               OP_LINKQ_WARM_ONE };
 void launch_case_batch(int storage, BatchOp op, const CaseArgs *cs, const int *map, int nblocks, hipStream_t s);
 // Launch sizes of the one-system boundary kernels (also the block ranges of
 // a system in the batched launches).
 int link_grid(const Params &p);
-int link_q_grid(const Params &p);
+// The link solver takes one lane per link (else eight) from a number of links
+// on; its grid for a system under either form.
+bool link_q_one(long long links);
+long long link_q_expected(const Params &p);
+int link_q_grid(const Params &p, bool one);
 
 }  // namespace mdl

@@ -154,3 +154,31 @@ def test_ensemble_with_one_warm_started_system(mdl):
         assert_same(sim, ref[:3], f"case {i}")
         assert np.array_equal(sim.links()[3], ref[3]), f"case {i}: link fractions differ"
     ens.close()
+
+
+def test_one_lane_per_link_gives_the_same_bits(mdl):
+    """Enough links in one launch that the link solver takes one lane per link
+    (32 768 expected ones, half as many again as there are plus 1024 a system);
+    alone each system has few and takes eight.  Both forms return the same
+    bits: also for waves that hold several bodies (six in a periodic box) and
+    where the points of a body reach half the box (an image per point)."""
+    cfgs = workloads.mini_ensemble(8) + [workloads.suspension_small(), workloads.comoving(n=24)]
+    steps = 8
+    expected, refs = 0, []
+    for c in cfgs:
+        sim = mdl.Simulation(c)
+        expected += 3 * len(sim.links()[0]) // 2 + 1024
+        sim.step(steps)
+        refs.append((sim.populations(), sim.owner(), sim.particles()))
+        q = sim.links()
+        refs[-1] += (q,)
+        sim.close()
+    print(f"expected links {expected}", flush=True)
+    assert expected >= 32768
+    ens = mdl.Ensemble(cfgs)
+    ens.step(steps)
+    for i, (sim, ref) in enumerate(zip(ens.cases, refs)):
+        assert_same(sim, ref[:3], f"case {i} ({cfgs[i].name})")
+        for a, b in zip(sim.links(), ref[3]):
+            assert np.array_equal(a, b), f"case {i}: links differ"
+    ens.close()
