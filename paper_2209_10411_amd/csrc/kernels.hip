@@ -124,15 +124,15 @@ __device__ __forceinline__ float stage_cp(CPs &c, int i, const double x[3], doub
     return fabsf(f.x) + fabsf(f.y) + fabsf(f.z);
 }
 
-// Whole block: the body's points (padded to a multiple of 4 with weight-0
-// copies of the first point) about the anchor X.
+// One wave: the body's points (padded to a multiple of 4 with
+// weight-0 copies of the first point) about the anchor X.
 __device__ void stage_cps(CPs &c, const DevParticle &P) {
     const int n4 = (P.n_cp + 3) & ~3;
-    const float b = threadIdx.x < n4 ? stage_cp(c, threadIdx.x, P.cpl[threadIdx.x < P.n_cp ? threadIdx.x : 0],
-                                                threadIdx.x < P.n_cp ? P.k[threadIdx.x] : 0.0, P.X)
-                                     : 0.f;
-    const float bw = wave_fmax(b);  // n4 <= 24 points: all in the first wave
-    if (threadIdx.x == 0) {
+    const int lane = threadIdx.x & 63;
+    const float b = lane < n4 ? stage_cp(c, lane, P.cpl[lane < P.n_cp ? lane : 0], lane < P.n_cp ? P.k[lane] : 0.0, P.X)
+                              : 0.f;
+    const float bw = wave_fmax(b);  // n4 <= 24 points: a lane each
+    if (lane == 0) {
         c.anc[0] = P.X[0]; c.anc[1] = P.X[1]; c.anc[2] = P.X[2];
         c.n = n4;
         c.img = P.img;
@@ -1592,8 +1592,8 @@ __global__ void k_refresh_pose(Params p, DevParticle *P, int fresh) {
     B.reach = fresh ? 0.0 : 1e30;
 }
 
-// Region node of a region kernel thread; false if outside the region or the
-// domain.
+// Region node of thread t of a region kernel's tile; false if outside the region
+// or the domain.
 // Local region coordinates of thread t of tile f (tiles of TILE_X x TILE_Y
 // x TILE_Z nodes over a region of dx x dy x ... nodes, x fastest).
 __device__ __forceinline__ void tile_local(int f, int dx, int dy, int t, int &lx, int &ly, int &lz) {
@@ -1629,12 +1629,12 @@ __device__ __forceinline__ bool tile_outside(const RegionMap &rm, const DevParti
 }
 
 __device__ __forceinline__ bool region_node(const Params &p, const RegionMap &rm,
-                                            const DevParticle *P, int bid, double rad, int &pi, int &x, int &y,
-                                            int &z, long long &n) {
+                                            const DevParticle *P, int bid, int t, double rad, int &pi, int &x,
+                                            int &y, int &z, long long &n) {
     pi = rm.part[bid];
     const int dx = rm.dims[3 * pi], dy = rm.dims[3 * pi + 1], dz = rm.dims[3 * pi + 2];
     int lx, ly, lz;
-    tile_local(rm.first[bid], dx, dy, threadIdx.x, lx, ly, lz);
+    tile_local(rm.first[bid], dx, dy, t, lx, ly, lz);
     if (lx >= dx || ly >= dy || lz >= dz) return false;
     const DevParticle &B = P[pi];
     if (!(B.full[0] | B.full[1] | B.full[2])) {
@@ -1664,26 +1664,108 @@ __device__ __forceinline__ bool region_node(const Params &p, const RegionMap &rm
 }
 
 // Flags (sec. 2.1): C >= 1 is solid; the owner is the lowest body index
-// (atomicMin).  own_new must hold FLUID on the region beforehand.
-__device__ __forceinline__ void mark_body(const Params &p, const RegionMap &rm, const DevParticle *P,
+// (atomicMin).  own_new must hold FLUID on the region beforehand.  A block of
+// TILE_Z / NZ waves per tile: lane (x, y) of a wave takes NZ nodes of the
+// tile's column along z, so a control point is read, and its distance in x
+// and y formed, once for NZ nodes; each wave stages the points for itself, so
+// there is no block barrier.  The decision is metaball_ge32's for each node
+// (its FP32 sum, the same bound, else FP64).  NZ = 4 does the least work, and
+// a tile outside the ball costs one wave: many tiles are bound by vector
+// issue (one reciprocal per node and point).  NZ = 1 has the shortest chain:
+// few tiles are bound by its latency.
+static_assert(TILE_X * TILE_Y == 64, "a tile's plane is one wave");
+template <int NZ>
+__device__ __forceinline__ void mark_tile(const Params &p, const RegionMap &rm, const DevParticle *P,
                                           int32_t *own_new, const int bid) {
-    __shared__ CPs cps;
+    constexpr int MARK_Z = NZ;
+    __shared__ CPs wave_cps[TILE_Z / NZ];
+    CPs &cps = wave_cps[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63, t0 = lane + 64 * NZ * (int)(threadIdx.x >> 6);
     const int bp = rm.part[bid];
     const double rad = flag_radius(P[bp]);
     if (tile_outside(rm, P[bp], bp, rm.first[bid], rad)) return;  // the whole block
     stage_cps(cps, P[bp]);
-    __syncthreads();
-    int pi, x, y, z;
-    long long n;
-    if (!region_node(p, rm, P, bid, rad, pi, x, y, z, n)) return;
-    const double xp[3] = {(double)x, (double)y, (double)z};
-    double Cf;
-    if (metaball_ge32(p, cps, xp, 1.0, Cf)) atomicMin(&own_new[n], pi);
+    wave_sync();
+    unsigned in = 0u;
+    int x = 0, y = 0, z[MARK_Z];
+    long long n[MARK_Z];
+#pragma unroll
+    for (int k = 0; k < MARK_Z; ++k) {
+        int pi, xk = 0, yk = 0;
+        z[k] = 0;
+        n[k] = 0;
+        if (region_node(p, rm, P, bid, t0 + 64 * k, rad, pi, xk, yk, z[k], n[k])) {
+            in |= 1u << k;
+            x = xk;  // the same for every node of the lane
+            y = yk;
+        }
+    }
+    if (!in) return;
+    // FP32 sums of the four nodes
+    double r0 = x - cps.anc[0], r1 = y - cps.anc[1];
+    unsigned far = 0u;  // differences could reach half a periodic box
+    const double room[3] = {0.5 * p.nx - 1.0, 0.5 * p.ny - 1.0, 0.5 * p.nz - 1.0};
+    if (cps.img) {
+        if (p.periodic & 1u) {
+            r0 = min_image_axis(r0, (double)p.nx, p.mi_up[0], p.mi_dn[0]);
+            if (!(fabs(r0) + (double)cps.bp < room[0])) far = ~0u;
+        }
+        if (p.periodic & 2u) {
+            r1 = min_image_axis(r1, (double)p.ny, p.mi_up[1], p.mi_dn[1]);
+            if (!(fabs(r1) + (double)cps.bp < room[1])) far = ~0u;
+        }
+    }
+    const float rx = (float)r0, ry = (float)r1;
+    float rz[MARK_Z], C[MARK_Z], rmin[MARK_Z];
+#pragma unroll
+    for (int k = 0; k < MARK_Z; ++k) {
+        double r2 = z[k] - cps.anc[2];
+        if (cps.img && (p.periodic & 4u)) {
+            r2 = min_image_axis(r2, (double)p.nz, p.mi_up[2], p.mi_dn[2]);
+            if (!(fabs(r2) + (double)cps.bp < room[2])) far |= 1u << k;
+        }
+        rz[k] = (float)r2;
+        C[k] = 0.f;
+        rmin[k] = 1.f;
+    }
+    for (int i0 = 0; i0 < cps.n; i0 += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float4 c = cps.f[i0 + u];
+            const float dx = rx - c.x, dy = ry - c.y, dxy = fmaf(dx, dx, dy * dy);
+#pragma unroll
+            for (int k = 0; k < MARK_Z; ++k) {
+                const float dz = rz[k] - c.z, d2 = fmaf(dz, dz, dxy);
+                rmin[k] = fminf(rmin[k], d2);
+                C[k] = fmaf(c.w, __builtin_amdgcn_rcpf(d2), C[k]);
+            }
+        }
+    }
+    unsigned open = 0u;
+#pragma unroll
+    for (int k = 0; k < MARK_Z; ++k) {
+        if (!((in >> k) & 1u)) continue;
+        const int side = !((far >> k) & 1u) && rmin[k] >= 1.f ? ge32_side(cps, rx, ry, rz[k], C[k], 1.0) : 0;
+        if (side > 0) atomicMin(&own_new[n[k]], bp);
+        if (side == 0) open |= 1u << k;
+    }
+    for (; open; open &= open - 1u) {  // rare: within the bound of the level, or near a control point
+        const int k = __ffs(open) - 1;
+        int zk = z[0];
+        long long nk = n[0];
+#pragma unroll
+        for (int q = 1; q < MARK_Z; ++q)
+            if (k == q) { zk = z[q]; nk = n[q]; }
+        const double xp[3] = {(double)x, (double)y, (double)zk};
+        double Cf;
+        if (metaball_ge(p, cps, xp, 1.0, Cf)) atomicMin(&own_new[nk], bp);
+    }
 }
 
-__global__ __launch_bounds__(BLK) void k_region_mark(Params p, RegionMap rm, const DevParticle *P,
-                                                     int32_t *own_new) {
-    mark_body(p, rm, P, own_new, blockIdx.x);
+template <int NZ>
+__global__ __launch_bounds__(64 * TILE_Z / NZ) void k_region_mark(Params p, RegionMap rm, const DevParticle *P,
+                                                                  int32_t *own_new) {
+    mark_tile<NZ>(p, rm, P, own_new, blockIdx.x);
 }
 
 // Integer sum over the 64 lanes of a wave (every lane gets it).
@@ -1701,21 +1783,6 @@ __device__ __forceinline__ int block_sum(int v, int *sh) {
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
     return sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-// Three block-wide sums at once (all BLK threads; sh3 LDS scratch).
-__device__ __forceinline__ void block_sum3(int &a, int &b, int &c, int (*sh3)[BLK]) {
-    a = wave_isum(a);
-    b = wave_isum(b);
-    c = wave_isum(c);
-    if ((threadIdx.x & 63) == 0) {
-        const int w = threadIdx.x >> 6;
-        sh3[0][w] = a; sh3[1][w] = b; sh3[2][w] = c;
-    }
-    __syncthreads();
-    a = sh3[0][0] + sh3[0][1] + sh3[0][2] + sh3[0][3];
-    b = sh3[1][0] + sh3[1][1] + sh3[1][2] + sh3[1][3];
-    c = sh3[2][0] + sh3[2][1] + sh3[2][2] + sh3[2][3];
 }
 
 // Boundary or uncovered node n = (x, y, z), one thread: pull the 19
@@ -1801,6 +1868,12 @@ __device__ void special_update(const Params &p, const typename Store<S>::T *__re
 //     special passes);
 //   - with blk_cnt set, the block also counts the cut links of the new flags
 //     for its body (first pass of the link build).
+// A block per tile.  Its time is the chain of loads of a tile (body, owners,
+// populations) and, in tiles along a surface, the instructions of the
+// boundary update: only a seventh of a wave's lanes hold such nodes there, so
+// the block first gathers them into one list (LDS) and one or two full waves
+// update them; the counts are ballots.  233 tiles: 17.5 -> 13.9 us; 46 673
+// tiles: 231 -> 218 us alone.
 template <int S>
 __device__ __forceinline__ void classify_body(const Params &p, const RegionMap &rm, const DevParticle *P,
                                               const int32_t *__restrict__ own_old,
@@ -1811,31 +1884,32 @@ __device__ __forceinline__ void classify_body(const Params &p, const RegionMap &
                                               const typename Store<S>::T *A,
                                               typename Store<S>::T *B, int do_special, int32_t *clear,
                                               const int bid) {
-    __shared__ int sh[BLK];
-    __shared__ int sh3[3][BLK];
-    // owners before / after over the tile and a one-node halo (beyond a wall: OUTSIDE)
+    // owners (before, after) over the tile and a one-node halo (beyond a wall: OUTSIDE)
     constexpr int HX = TILE_X + 2, HY = TILE_Y + 2, HN = HX * HY * (TILE_Z + 2);
     constexpr int32_t OUTSIDE = -2;
-    __shared__ int32_t h_old[HN], h_new[HN];
-    const double rad = class_radius(P[rm.part[bid]]);
-    if (tile_outside(rm, P[rm.part[bid]], rm.part[bid], rm.first[bid], rad)) {  // the whole block
-        if (blk_cnt && threadIdx.x == 0) blk_cnt[bid] = 0;
+    __shared__ int2 h_own[HN];
+    __shared__ uint32_t s_wall[BLK], s_solid[BLK];  // boundary and uncovered nodes: masks, the thread on top
+    __shared__ int s_any[BLK / 64], s_sum[4][BLK / 64], s_spec;
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int bp = rm.part[bid];
+    const DevParticle &Bp = P[bp];
+    const double rad = class_radius(Bp);
+    if (tile_outside(rm, Bp, bp, rm.first[bid], rad)) {  // the whole block
+        if (blk_cnt && t == 0) blk_cnt[bid] = 0;
         return;
     }
+    int bx, by, bz;  // the tile's first node in the region
+    tile_local(rm.first[bid], rm.dims[3 * bp], rm.dims[3 * bp + 1], 0, bx, by, bz);
+    const int L[3] = {p.nx, p.ny, p.nz};
+    bool any = false;
     {
-        const int bp = rm.part[bid];
-        const int dx = rm.dims[3 * bp], dy = rm.dims[3 * bp + 1];
-        int bx, by, bz;
-        tile_local(rm.first[bid], dx, dy, 0, bx, by, bz);
-        const DevParticle &Bp = P[bp];
-        const int L[3] = {p.nx, p.ny, p.nz};
         // all of a thread's halo loads are issued before the first is
         // written to LDS (one memory round trip, not one per slot)
         constexpr int HR = (HN + BLK - 1) / BLK;
         int32_t vo[HR], vn[HR];
 #pragma unroll
         for (int r = 0; r < HR; ++r) {
-            const int h = threadIdx.x + r * BLK;
+            const int h = t + r * BLK;
             int c[3] = {Bp.lo[0] + bx - 1 + h % HX, Bp.lo[1] + by - 1 + (h / HX) % HY, Bp.lo[2] + bz - 1 + h / (HX * HY)};
             bool ok = h < HN;
             for (int a = 0; a < 3; ++a)
@@ -1849,37 +1923,42 @@ __device__ __forceinline__ void classify_body(const Params &p, const RegionMap &
         }
 #pragma unroll
         for (int r = 0; r < HR; ++r) {
-            const int h = threadIdx.x + r * BLK;
-            if (h < HN) {
-                h_old[h] = vo[r];
-                h_new[h] = vn[r];
-            }
+            const int h = t + r * BLK;
+            if (h < HN) h_own[h] = make_int2(vo[r], vn[r]);
+            any |= (vo[r] != OUTSIDE && vo[r] != FLUID) || (vn[r] != OUTSIDE && vn[r] != FLUID);
         }
     }
+    const bool wave_any = __any(any);
+    if (lane == 0) s_any[w] = wave_any;
+    if (t == 0) s_spec = 0;
     __syncthreads();
     int pi, x, y, z;
     long long n;
-    const bool in = region_node(p, rm, P, bid, rad, pi, x, y, z, n);
+    const bool in = region_node(p, rm, P, bid, t, rad, pi, x, y, z, n);
     if (in && clear) clear[n] = FLUID;  // the dead flag buffer (the flags before own_old) for the next flagging
+    if (!(s_any[0] | s_any[1] | s_any[2] | s_any[3])) {  // no solid node in reach: plain fluid, the whole block
+        if (in) skip_next[n] = 0;
+        if (blk_cnt && t == 0) blk_cnt[bid] = 0;
+        return;
+    }
     uint32_t m = 0u, wall = 0u, solid = 0u;
     // owners before / after, lowest owner among the neighbours before / after
     int32_t oo = FLUID, on = FLUID, mo = FLUID, mn = FLUID;
     if (in) {
-        const int t = threadIdx.x;
         const int hc = (t % TILE_X + 1) + HX * ((t / TILE_X) % TILE_Y + 1) + HX * HY * (t / (TILE_X * TILE_Y) + 1);
-        oo = h_old[hc];
-        on = h_new[hc];
+        const int2 self = h_own[hc];
+        oo = self.x;
+        on = self.y;
 #pragma unroll
         for (int i = 1; i < Q; ++i) {
-            const int hs = hc - EX[i] - HX * EY[i] - HX * HY * EZ[i];
-            const int32_t vo = h_old[hs], vn = h_new[hs];
-            if (vo == OUTSIDE) {
+            const int2 v = h_own[hc - EX[i] - HX * EY[i] - HX * HY * EZ[i]];
+            if (v.x == OUTSIDE) {
                 wall |= 1u << i;
             } else {
-                mo = min(mo, vo);
-                mn = min(mn, vn);
-                if (vo != FLUID) solid |= 1u << i;
-                if (vn == pi) m |= 1u << i;
+                mo = min(mo, v.x);
+                mn = min(mn, v.y);
+                if (v.x != FLUID) solid |= 1u << i;
+                if (v.y == pi) m |= 1u << i;
             }
         }
     }
@@ -1888,37 +1967,60 @@ __device__ __forceinline__ void classify_body(const Params &p, const RegionMap &
     if (sn) m = 0u;
     bool act = in;
     if (act) act = sn ? on == pi : so ? oo == pi : onb == FLUID || onb == pi;
-    int c_solid = 0, c_refill = 0, c_spec = 0;
-    if (act) {
-        skip_next[n] = (uint8_t)((sn || nb_new) ? 1 : 0);
-        const bool lo = !so && nb_old;
-        const bool spec = !sn && (so || lo);
-        c_solid = sn;
-        // a re-flag (no boundary update) lists and counts its uncovered nodes
-        // over the whole domain instead (k_uncovered): a body moved from
-        // outside may leave them outside its new region
-        c_refill = !sn && so && do_special;
-        c_spec = do_special ? spec : lo && !sn;
-        if (spec && do_special) {
-            if (so && (oo < 0 || oo >= p.np)) atomicOr(&cnt->err, ERR_BAD_INDEX);  // never expected
-            else special_update<S>(p, A, B, P, x, y, z, n, wall, solid, oo);
+    if (act) skip_next[n] = (uint8_t)((sn || nb_new) ? 1 : 0);
+    const bool lo = !so && nb_old;
+    const bool spec = act && !sn && (so || lo);
+    // a re-flag (no boundary update) lists and counts its uncovered nodes
+    // over the whole domain instead (k_uncovered): a body moved from
+    // outside may leave them outside its new region
+    const unsigned long long b_solid = __ballot(act && sn), b_refill = __ballot(act && !sn && so && do_special),
+                             b_spec = __ballot(do_special ? spec : act && lo && !sn);
+    if (lane == 0) {
+        s_sum[0][w] = __popcll(b_solid);
+        s_sum[1][w] = __popcll(b_refill);
+        s_sum[2][w] = __popcll(b_spec);
+    }
+    // the boundary and uncovered nodes (a few lanes of each wave along the
+    // surface) are gathered into one list, so that the update fills its waves
+    if (do_special && b_spec) {  // wave-uniform
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&s_spec, __popcll(b_spec));
+        base = __shfl(base, 0);
+        if (spec) {
+            const int k = base + __popcll(b_spec & ((1ull << lane) - 1ull));
+            s_wall[k] = wall;
+            s_solid[k] = solid | ((uint32_t)t << 24);
         }
     }
-    // per-body node counts (one atomic per block and count, integers: order-free)
-    block_sum3(c_solid, c_refill, c_spec, sh3);
-    if (threadIdx.x == 0) {
-        int *bs = body_stats + 4 * rm.part[bid];
-        if (c_solid) atomicAdd(bs + 1, c_solid);
-        if (c_refill) atomicAdd(bs + 2, c_refill);
-        if (c_spec) atomicAdd(bs + 3, c_spec);
+    if (blk_cnt) {  // first pass of the link build: this body's cut links of the new flags
+        lmask[bid * BLK + t] = m;
+        const int c = __popc(m);  // 0..18: five bits, a ballot each
+        int s = 0;
+#pragma unroll
+        for (int b = 0; b < 5; ++b) s += __popcll(__ballot((c >> b) & 1)) << b;
+        if (lane == 0) s_sum[3][w] = s;
     }
-    if (!blk_cnt) return;
-    // first pass of the link build: this body's cut links of the new flags
-    lmask[bid * BLK + threadIdx.x] = m;
-    const int s = block_sum(__popc(m), sh);
-    if (threadIdx.x == 0) {
-        blk_cnt[bid] = s;
-        if (s) atomicAdd(body_stats + 4 * rm.part[bid], s);
+    __syncthreads();
+    if (t < 4) {  // per-body counts (one atomic per block and count, integers: order-free)
+        const int k = t == 0 ? 3 : t - 1;  // slots: cut links, solid, uncovered, special
+        const int c = s_sum[k][0] + s_sum[k][1] + s_sum[k][2] + s_sum[k][3];
+        if (t > 0 || blk_cnt) {
+            if (t == 0) blk_cnt[bid] = c;
+            if (c) atomicAdd(body_stats + 4 * bp + t, c);
+        }
+    }
+    if (!do_special) return;
+    for (int k = t; k < s_spec; k += BLK) {
+        const uint32_t sw = s_wall[k], ss = s_solid[k];
+        const int ts = (int)(ss >> 24);
+        const int lx = ts % TILE_X, ly = (ts / TILE_X) % TILE_Y, lz = ts / (TILE_X * TILE_Y);
+        const int32_t owner = h_own[(lx + 1) + HX * (ly + 1) + HX * HY * (lz + 1)].x;
+        int c[3] = {Bp.lo[0] + bx + lx, Bp.lo[1] + by + ly, Bp.lo[2] + bz + lz};
+        for (int a = 0; a < 3; ++a)
+            if (c[a] < 0 || c[a] >= L[a]) c[a] = ((c[a] % L[a]) + L[a]) % L[a];
+        const long long ns = (long long)c[0] + (long long)p.nx * ((long long)c[1] + (long long)p.ny * c[2]);
+        if (owner != FLUID && (owner < 0 || owner >= p.np)) atomicOr(&cnt->err, ERR_BAD_INDEX);  // never expected
+        else special_update<S>(p, A, B, P, c[0], c[1], c[2], ns, sw, ss & 0xffffffu, owner);
     }
 }
 
@@ -2077,129 +2179,100 @@ __global__ void k_fill_u8(uint8_t *a, long long n, uint8_t v) {
         a[i] = v;
 }
 
-// Link build, second pass: each block finds its offset in the particle-major
-// list from the link totals of the bodies before its own and the counts of
-// its body's earlier blocks (the first block of a body also records the
-// body's offset, the last block the total) and lists
-// its links (masks from the classification; thread order, then direction
-// order).  The link fractions follow in k_link_q.
-__device__ __forceinline__ void emit_body(const Params &p, const RegionMap &rm, const DevParticle *P,
-                                          const uint32_t *__restrict__ lmask,
-                                          const int *__restrict__ blk_cnt,
+// Link build, second pass, one wave per tile: the tile's offset in the
+// particle-major list from the link totals of the bodies before its own and
+// the counts of its body's earlier tiles (a body's first tile also records
+// the body's offset, the last tile the total), then its links (masks from the
+// classification, four threads' masks per lane; thread order, then direction
+// order).  Masks and counts are loaded together: one memory round trip per
+// tile, no barrier.  The link fractions follow in k_link_q.
+__device__ __forceinline__ void emit_tile(const Params &p, const RegionMap &rm, const DevParticle *P,
+                                          const uint32_t *__restrict__ lmask, const int *__restrict__ blk_cnt,
                                           const int *__restrict__ body_stats,
                                           const int *__restrict__ part_first_blk, int *__restrict__ l_off,
                                           uint32_t *__restrict__ l_node, uint32_t *__restrict__ l_do,
-                                          Counters *cnt, int32_t *clear, const int bid, const int nblk) {
-    __shared__ int sh[BLK];
-    const int t = threadIdx.x;
-    const int pid = rm.part[bid];
-    const double rad = class_radius(P[pid]);
-    // a block with no node in the ball lists nothing (its classification
-    // counted none); the first block of a body and the last block still
-    // record the offsets
-    if (tile_outside(rm, P[pid], pid, rm.first[bid], rad) && part_first_blk[pid] != bid && bid != nblk - 1) return;
-    // nor does a tile without links when the dead flags were cleared by the
-    // classification (clear == NULL)
-    if (!clear && blk_cnt[bid] == 0 && part_first_blk[pid] != bid && bid != nblk - 1) return;
-    // the tile's own mask is loaded together with the counts before it (one
-    // memory round trip for both)
-    int pi, x, y, z;
-    long long n;
-    const bool in = region_node(p, rm, P, bid, rad, pi, x, y, z, n);
-    const uint32_t m = in ? lmask[bid * BLK + t] : 0u;
+                                          Counters *cnt, const int bid, const int nblk) {
+    const int lane = threadIdx.x & 63;
+    const int pid = rm.part[bid], here = blk_cnt[bid], first = part_first_blk[pid];
+    if (here == 0 && first != bid && bid != nblk - 1) return;
+    // the masks hold this classification's links only where the tile has some
+    const uint4 m4 = ((const uint4 *)(lmask + (size_t)bid * BLK))[lane];
     int before = 0;
-    for (int q = t; q < pid; q += BLK) before += body_stats[4 * q];
-    for (int b = part_first_blk[pid] + t; b < bid; b += BLK) before += blk_cnt[b];
-    const int base = block_sum(before, sh);
-    __syncthreads();  // every thread has read the sum before sh is reused
-    if (t == 0) {
-        if (part_first_blk[pid] == bid) l_off[pid] = min(base, p.link_cap);
+    for (int q = lane; q < pid; q += 64) before += body_stats[4 * q];
+    for (int b = first + lane; b < bid; b += 64) before += blk_cnt[b];
+    const int base = wave_isum(before);
+    if (lane == 0) {
+        if (first == bid) l_off[pid] = min(base, p.link_cap);
         if (bid == nblk - 1) {
-            const int total = base + blk_cnt[bid];
+            const int total = base + here;
             if (total > p.link_cap) atomicOr(&cnt->err, ERR_LINK_OVERFLOW);
             cnt->n_links = min(total, p.link_cap);
             l_off[p.np] = min(total, p.link_cap);
         }
     }
-    if (in && clear) clear[n] = FLUID;
-    // exclusive prefix of the link counts over the block: inclusive scan
-    // within the wave, plus the totals of the earlier waves
-    const int c = __popc(m), lane = t & 63, w = t >> 6;
+    if (here == 0) return;
+    const uint32_t m[4] = {m4.x, m4.y, m4.z, m4.w};
+    const int c = __popc(m[0]) + __popc(m[1]) + __popc(m[2]) + __popc(m[3]);
     int incl = c;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int v = __shfl_up(incl, d);
         if (lane >= d) incl += v;
     }
-    if (lane == 63) sh[w] = incl;
-    __syncthreads();
-    int wbase = 0;
-    for (int k = 0; k < w; ++k) wbase += sh[k];
-    int o = base + wbase + incl - c;
-    for (int i = 1; i < Q; ++i)
-        if ((m >> i) & 1u) {
+    if (!c) return;
+    int o = base + incl - c;
+    const DevParticle &B = P[pid];
+    int lx, ly, lz;
+    tile_local(rm.first[bid], rm.dims[3 * pid], rm.dims[3 * pid + 1], 4 * lane, lx, ly, lz);
+    const int L[3] = {p.nx, p.ny, p.nz};
+    int q[3] = {B.lo[0] + lx, B.lo[1] + ly, B.lo[2] + lz};
+    for (int a = 1; a < 3; ++a)  // a node with links lies in the domain or wraps into it
+        if (q[a] < 0 || q[a] >= L[a]) q[a] = ((q[a] % L[a]) + L[a]) % L[a];
+    const uint32_t row = (uint32_t)(p.nx * ((long long)q[1] + (long long)p.ny * q[2]));
+    const uint32_t who = (uint32_t)pid << 8;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // four consecutive x of one row
+        int x = q[0] + k;
+        if (x < 0 || x >= L[0]) x = ((x % L[0]) + L[0]) % L[0];
+        for (uint32_t w = m[k]; w; w &= w - 1u, ++o)
             if (o < p.link_cap) {
-                l_node[o] = (uint32_t)n;
-                l_do[o] = (uint32_t)i | ((uint32_t)pid << 8);
+                l_node[o] = row + (uint32_t)x;
+                l_do[o] = (uint32_t)(__ffs(w) - 1) | who;
             }
-            ++o;
-        }
-}
-
-// The link list runs beside the stream-collide, which holds most of the
-// compute units: a kernel there keeps few blocks resident, and one block per
-// region tile (tens of thousands, nearly all without links) took the whole
-// length of the stream-collide.  Here a block of a grid of G visits tiles b,
-// b + G, b + 2G, ... ; per round, wave 0 tests 64 of them at once (one lane
-// each) and the block then runs the per-tile body for the ones that pass,
-// one after another.  (The flagging and the classification, which run alone
-// and have work in a third of their tiles, are faster with a block per tile:
-// this form took them from 122 to 191 and from 268 to 512 us.)
-constexpr int REGION_GRID = 2048;
-inline int region_grid(const Params &p) { return p.region_blocks < REGION_GRID ? p.region_blocks : REGION_GRID; }
-
-template <class Test, class Body>
-__device__ __forceinline__ void visit_tiles(int nblk, Test test, Body body) {
-    __shared__ unsigned long long sel;
-    const int G = gridDim.x;
-    for (int base = blockIdx.x; base < nblk; base += 64 * G) {
-        if (threadIdx.x < 64) {
-            const int b = base + threadIdx.x * G;
-            const unsigned long long m = __ballot(b < nblk && test(b));
-            if (threadIdx.x == 0) sel = m;
-        }
-        __syncthreads();
-        unsigned long long m = sel;
-        __syncthreads();  // sel is rewritten in the next round
-        while (m) {
-            const int j = __ffsll((long long)m) - 1;
-            m &= m - 1;
-            body(base + j * G);
-            __syncthreads();  // the body's LDS is restaged for the next tile
-        }
     }
 }
+static_assert(TILE_X % 4 == 0, "a lane's four threads share a row");
 
-// The link list over the tiles with links, each body's first tile and the
-// last tile (they record the offsets); the dead flags were cleared by the
-// classification.
-__global__ __launch_bounds__(BLK) void k_link_emit_tiles(Params p, RegionMap rm, const DevParticle *P,
+// The link list runs beside the stream-collide, which holds most of the
+// compute units: a launch there keeps few blocks resident, and one block per
+// region tile (tens of thousands, nearly all without links) took the whole
+// length of the stream-collide.  Here wave w of a grid of W waves visits tiles
+// w, w + W, w + 2 W, ...; it tests 64 of them at once (one lane each) and
+// lists the ones with links, each body's first tile and the last tile (they
+// record the offsets), one after another.  46 673 tiles of 200 bodies: 118 us
+// with a block of four waves per tile (three barriers and four dependent
+// loads each).
+constexpr int REGION_GRID = 2048;
+inline int emit_grid(const Params &p) { return min((p.region_blocks + 3) / 4, REGION_GRID); }
+
+__global__ __launch_bounds__(256) void k_link_emit_tiles(Params p, RegionMap rm, const DevParticle *P,
                                                          const uint32_t *__restrict__ lmask,
                                                          const int *__restrict__ blk_cnt,
                                                          const int *__restrict__ body_stats,
                                                          const int *__restrict__ part_first_blk,
                                                          int *__restrict__ l_off, uint32_t *__restrict__ l_node,
                                                          uint32_t *__restrict__ l_do, Counters *cnt) {
-    const int nblk = p.region_blocks;
-    visit_tiles(
-        nblk,
-        [&](int b) {  // a body's tiles are consecutive: its first tile follows another body's
-            return blk_cnt[b] > 0 || b == 0 || rm.part[b - 1] != rm.part[b] || b == nblk - 1;
-        },
-        [&](int b) {
-            emit_body(p, rm, P, lmask, blk_cnt, body_stats, part_first_blk, l_off, l_node, l_do, cnt, nullptr, b,
-                      nblk);
-        });
+    const int nblk = p.region_blocks, W = gridDim.x * 4;
+    const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    for (int base = w; base < nblk; base += 64 * W) {
+        const long long b = base + (long long)(threadIdx.x & 63) * W;
+        // a body's tiles are consecutive: its first tile follows another body's
+        unsigned long long m = __ballot(b < nblk && (blk_cnt[b] > 0 || b == 0 || rm.part[b - 1] != rm.part[b] ||
+                                                     b == nblk - 1));
+        for (; m; m &= m - 1)
+            emit_tile(p, rm, P, lmask, blk_cnt, body_stats, part_first_blk, l_off, l_node, l_do, cnt,
+                      base + (__ffsll((long long)m) - 1) * W, nblk);
+    }
 }
 
 // Link build, third pass: the link fractions of the whole list, G lanes per
@@ -2463,10 +2536,11 @@ __global__ __launch_bounds__(256) void k_rigid_batch(const CaseArgs *__restrict_
     rigid_case(a.p, a.P, a.cb, a.cnt);
 }
 
-__global__ __launch_bounds__(BLK) void k_region_mark_batch(const CaseArgs *__restrict__ cs,
-                                                           const int *__restrict__ map) {
+template <int NZ>
+__global__ __launch_bounds__(64 * TILE_Z / NZ) void k_region_mark_batch(const CaseArgs *__restrict__ cs,
+                                                                        const int *__restrict__ map) {
     const CaseArgs &a = cs[map[blockIdx.x]];
-    mark_body(a.p, a.rm, a.P, a.own_new, (int)blockIdx.x - a.first[BK_REGION]);
+    mark_tile<NZ>(a.p, a.rm, a.P, a.own_new, (int)blockIdx.x - a.first[BK_REGION]);
 }
 
 // with the boundary/uncovered update and the link count of the new flags
@@ -2476,14 +2550,14 @@ __global__ __launch_bounds__(BLK) void k_region_classify_batch(const CaseArgs *_
     using T = typename Store<S>::T;
     const CaseArgs &a = cs[map[blockIdx.x]];
     classify_body<S>(a.p, a.rm, a.P, a.own_old, a.own_new, a.skip_next, a.special, a.cnt, a.blk_cnt, a.lmask,
-                     a.body_stats, (const T *)a.A, (T *)a.B, 1, nullptr, (int)blockIdx.x - a.first[BK_REGION]);
+                     a.body_stats, (const T *)a.A, (T *)a.B, 1, a.own_dead, (int)blockIdx.x - a.first[BK_REGION]);
 }
 
-__global__ __launch_bounds__(BLK) void k_link_emit_batch(const CaseArgs *__restrict__ cs,
-                                                         const int *__restrict__ map) {
+__global__ __launch_bounds__(64) void k_link_emit_batch(const CaseArgs *__restrict__ cs,
+                                                        const int *__restrict__ map) {
     const CaseArgs &a = cs[map[blockIdx.x]];
-    emit_body(a.p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats, a.part_first_blk, a.l_off, a.l_node, a.l_do, a.cnt,
-              a.own_dead, (int)blockIdx.x - a.first[BK_REGION], a.nblk[BK_REGION]);
+    emit_tile(a.p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats, a.part_first_blk, a.l_off, a.l_node, a.l_do, a.cnt,
+              (int)blockIdx.x - a.first[BK_REGION], a.nblk[BK_REGION]);
 }
 
 __global__ __launch_bounds__(256) void k_link_guess_batch(const CaseArgs *__restrict__ cs,
@@ -2502,6 +2576,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 
 // ------------------------------------------------------------ host launchers
 static inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
+
+// Tiles from which the flagging takes a column of four nodes per lane: 2048
+// tiles of four waves are eight waves per SIMD, all that are resident; beyond,
+// they run in rounds and the work counts (46 673 tiles: 131 -> 67 us beside the
+// stream-collide), below, the chain does (233 tiles: 7.3 against 11.6 us).
+constexpr int MARK_COLUMNS = 2048;
 
 // list kernels stride over their lists; size their grids for the expected lengths
 static int expected_links(const Params &p) { return p.est_links > 0 ? min(p.est_links, p.link_cap) : p.link_cap; }
@@ -2573,7 +2653,11 @@ static void launch_step_kernels_t(const StepArgs &a) {
         }
     } else if (a.phase == PHASE_FLAGS) {
         if (p.np > 0) {
-            if (a.move) k_region_mark<<<p.region_blocks, BLK, 0, a.stream>>>(p, a.rm, a.P, a.own_new);
+            if (a.move) {
+                const int nb = p.region_blocks;
+                if (nb >= MARK_COLUMNS) k_region_mark<4><<<nb, 64, 0, a.stream>>>(p, a.rm, a.P, a.own_new);
+                else k_region_mark<1><<<nb, 256, 0, a.stream>>>(p, a.rm, a.P, a.own_new);
+            }
             hipExtLaunchKernelGGL(k_region_classify<S>, dim3(p.region_blocks), dim3(BLK), 0, a.stream, nullptr,
                                   a.ev_stop, 0, p, a.rm, (const DevParticle *)a.P, (const int32_t *)a.own_old,
                                   (const int32_t *)a.own_new, a.skip_next, a.special, a.cnt,
@@ -2617,7 +2701,7 @@ static void launch_step_kernels_t(const StepArgs &a) {
             (void)hipEventRecord(a.ev_stop, a.stream);
     } else if (a.phase == PHASE_LINKBUILD) {
         if (p.np > 0) {
-            k_link_emit_tiles<<<region_grid(p), BLK, 0, a.stream>>>(p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats,
+            k_link_emit_tiles<<<emit_grid(p), 256, 0, a.stream>>>(p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats,
                                                                      a.part_first_blk, a.l_off, a.l_node, a.l_do,
                                                                      a.cnt);
             const bool one = link_q_one(link_q_expected(p));
@@ -2675,9 +2759,12 @@ static void launch_case_batch_t(BatchOp op, const CaseArgs *cs, const int *map, 
         case OP_LINKS: k_links_batch<S><<<nblocks, 256, 0, s>>>(cs, map); break;
         case OP_REDUCE: k_reduce_batch<<<nblocks, 256, 0, s>>>(cs, map); break;
         case OP_RIGID: k_rigid_batch<<<nblocks, 256, 0, s>>>(cs, map); break;
-        case OP_MARK: k_region_mark_batch<<<nblocks, BLK, 0, s>>>(cs, map); break;
+        case OP_MARK:
+            if (nblocks >= MARK_COLUMNS) k_region_mark_batch<4><<<nblocks, 64, 0, s>>>(cs, map);
+            else k_region_mark_batch<1><<<nblocks, 256, 0, s>>>(cs, map);
+            break;
         case OP_CLASSIFY: k_region_classify_batch<S><<<nblocks, BLK, 0, s>>>(cs, map); break;
-        case OP_EMIT: k_link_emit_batch<<<nblocks, BLK, 0, s>>>(cs, map); break;
+        case OP_EMIT: k_link_emit_batch<<<nblocks, 64, 0, s>>>(cs, map); break;
         case OP_LINKQ: k_link_q_batch<false, 8><<<nblocks, 256, 0, s>>>(cs, map); break;
         case OP_LINKQ_ONE: k_link_q_batch<false, 1><<<nblocks, 256, 0, s>>>(cs, map); break;
         case OP_LINKQ_WARM:  // guesses of the systems with a network, then every solve
