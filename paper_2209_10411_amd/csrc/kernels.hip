@@ -48,6 +48,21 @@ __constant__ double c_wd[Q] = {1.0 / 3,  1.0 / 18, 1.0 / 18, 1.0 / 18, 1.0 / 18,
                                1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36,
                                1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36, 1.0 / 36};
 
+// Block b of G takes item xcd_order(b, G).  The hardware deals consecutive
+// blocks out to the eight XCDs in turn; here XCD k takes the k-th eighth of the
+// items, so that items next to each other, which share cache lines, meet in one
+// L2 (a region tile is 8 nodes wide, a quarter of a 128-byte line of a
+// population).  A permutation of 0 .. G - 1 for any G.  200 bodies in 256^3:
+// the classification fetches 485 MB instead of 912 (272 -> 253 us under the
+// counters), the bounce-back 458 instead of 970 (163 -> 146 us).  The
+// ensemble's launches keep the hardware's order: beside its stream-collide
+// this one was 1 % slower.
+constexpr int N_XCD = 8;
+__device__ __forceinline__ int xcd_order(int b, int G) {
+    const int k = b % N_XCD, q = G / N_XCD, r = G % N_XCD;
+    return k * q + min(k, r) + b / N_XCD;
+}
+
 __device__ __forceinline__ void node_xyz(const Params &p, long long n, int &x, int &y, int &z) {
     if (p.N <= 0xffffffffLL) {  // 32-bit quotients (far shorter than 64-bit division)
         const unsigned u = (unsigned)n, r = u / (unsigned)p.nx;
@@ -631,7 +646,10 @@ __device__ __forceinline__ void links_body(const Params &p, const typename Store
     const int t = threadIdx.x, lane = t & 63;
     const int nl = cnt->n_links;
     const int nblock = (nl + 255) >> 8;  // 256 links per block and round, a chunk of 64 per wave
-    for (int cb = bid; cb < nblock; cb += nblk) {
+    // each XCD takes one eighth of the list (links next to each other in it read
+    // the same lines of the populations)
+    const int eighth = (nblock + N_XCD - 1) / N_XCD, end = min(nblock, (bid % N_XCD + 1) * eighth);
+    for (int cb = bid % N_XCD * eighth + bid / N_XCD; cb < end; cb += max(1, nblk / N_XCD)) {
         const int l = (cb << 8) + t, ch = l >> 6;
         double dP[3] = {0, 0, 0}, dT[3] = {0, 0, 0};
         int pi = -1;
@@ -1765,7 +1783,7 @@ __device__ __forceinline__ void mark_tile(const Params &p, const RegionMap &rm, 
 template <int NZ>
 __global__ __launch_bounds__(64 * TILE_Z / NZ) void k_region_mark(Params p, RegionMap rm, const DevParticle *P,
                                                                   int32_t *own_new) {
-    mark_tile<NZ>(p, rm, P, own_new, blockIdx.x);
+    mark_tile<NZ>(p, rm, P, own_new, xcd_order(blockIdx.x, gridDim.x));
 }
 
 // Integer sum over the 64 lanes of a wave (every lane gets it).
@@ -2035,7 +2053,7 @@ __global__ __launch_bounds__(BLK) void k_region_classify(Params p, RegionMap rm,
                                                          typename Store<S>::T *B, int do_special,
                                                          int32_t *clear) {
     classify_body<S>(p, rm, P, own_old, own_new, skip_next, special, cnt, blk_cnt, lmask, body_stats, A, B,
-                     do_special, clear, blockIdx.x);
+                     do_special, clear, xcd_order(blockIdx.x, gridDim.x));
 }
 
 // Nodes uncovered by a re-flag (solid before, fluid after) anywhere in the
@@ -2519,7 +2537,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // system map[b] as its block b - first[kind] (the same code as the
 // one-system launches above).
 template <int S>
-__global__ __launch_bounds__(256) void k_links_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_links_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
     using T = typename Store<S>::T;
     const CaseArgs &a = cs[map[blockIdx.x]];
     links_body<S>(a.p, (const T *)a.A, (T *)a.B, a.own_old, a.P, a.l_node, a.l_do, a.l_q, a.part, a.cnt,
@@ -2585,7 +2603,8 @@ constexpr int MARK_COLUMNS = 2048;
 
 // list kernels stride over their lists; size their grids for the expected lengths
 static int expected_links(const Params &p) { return p.est_links > 0 ? min(p.est_links, p.link_cap) : p.link_cap; }
-int link_grid(const Params &p) { return max(1, min(cdiv(expected_links(p), 256), 2048)); }
+// a multiple of the XCDs: each takes its share of the list
+int link_grid(const Params &p) { return N_XCD * max(1, min(cdiv(expected_links(p), 256 * N_XCD), 1024)); }
 // G = 8 below LINKQ_ONE links: 4096 waves of eight links are four per SIMD, as
 // many as are resident; beyond, they run in rounds and G = 1 is the shorter.
 constexpr int LINKQ_ONE = 32768;
