@@ -969,20 +969,24 @@ lbm_status lbm_set_populations(lbm_ctx *c, const double *f, int32_t post_collisi
 
 lbm_status lbm_get_macros(lbm_ctx *c, double *rho, double *u) {
     if (!c || !rho || !u) return fail(LBM_E_INVALID, "NULL argument");
-    const long long N = c->pl.N;
-    std::vector<double> f((size_t)Q * N);
-    lbm_status s = read_state(c, f.data());
+    lbm_status s = check_device(c);
     if (s) return s;
-    for (long long n = 0; n < N; ++n) {
-        double r = 0, j[3] = {0, 0, 0};
-        for (int i = 0; i < Q; ++i) {
-            const double v = f[(size_t)i * N + n];
-            r += v;
-            j[0] += EX[i] * v; j[1] += EY[i] * v; j[2] += EZ[i] * v;
-        }
-        rho[n] = r;
-        for (int a = 0; a < 3; ++a) u[3 * n + a] = j[a] / r - 0.5 * c->p.gfd[a];
+    // The fields pass through the next flag buffer (4 bytes a node, 32 a node
+    // needed: nine turns at most), which is all FLUID between steps and is made
+    // so again: no other memory of the arena is free for them.
+    const long long N = c->pl.N, chunk = std::max<long long>(1, 4 * N / 32);
+    double *drho = (double *)c->own[c->in];
+    hipError_t e = hipSuccess;
+    for (long long n0 = 0; n0 < N && e == hipSuccess; n0 += chunk) {
+        const long long m = std::min(chunk, N - n0);
+        launch_macros(c->p, c->A, n0, m, drho, drho + m, c->stream);
+        if ((e = hipGetLastError()) == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) e = hipMemcpy(rho + n0, drho, 8 * m, hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(u + 3 * n0, drho + m, 24 * m, hipMemcpyDeviceToHost);
     }
+    launch_fill_i32(c->own[c->in], N, FLUID, c->stream);
+    HIPCHK(e);
+    HIPCHK(hipGetLastError());
     return LBM_OK;
 }
 

@@ -2186,6 +2186,32 @@ __global__ void k_collide_stored(Params p, typename Store<S>::T *A, const int32_
     }
 }
 
+// Density and velocity of the nodes n0 .. n0 + count of the stored state, FP64: the moments of
+// f_i = d_i + w_i rho0 summed in direction order without contraction (the sums
+// of a plain evaluation).  One node per lane, bound by HBM (19 populations in,
+// 32 bytes out); what the host then waits for is the copy of those 32 bytes a
+// node, where it took the 19 populations and formed the sums itself
+// (96x96x161, FP32: 119 -> 4.6 ms a call, 3 ms of it the copy, the rest the caller's new pages).
+template <int S>
+__global__ __launch_bounds__(256) void k_macros(Params p, const typename Store<S>::T *__restrict__ A, long long n0,
+                                                long long count, double *__restrict__ rho, double *__restrict__ u) {
+#pragma clang fp contract(off)
+    const long long k = blockIdx.x * 256ll + threadIdx.x, n = n0 + k;
+    if (k >= count || n >= p.N) return;
+    double r = 0.0, j[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const double d = (double)Store<S>::ld(A, pidx(n, i), 1.f) * (double)p.inv_scale;
+        const double v = d + WD[i] * p.rho0;
+        r += v;
+        j[0] += EX[i] * v;
+        j[1] += EY[i] * v;
+        j[2] += EZ[i] * v;
+    }
+    rho[k] = r;
+    for (int a = 0; a < 3; ++a) u[3 * k + a] = j[a] / r - 0.5 * p.gfd[a];
+}
+
 __global__ void k_reset_counters(Counters *cnt) { reset_step_counters(cnt); }
 
 __global__ void k_fill_i32(int32_t *a, long long n, int32_t v) {
@@ -2802,6 +2828,14 @@ void launch_case_batch(int storage, BatchOp op, const CaseArgs *cs, const int *m
     if (storage == 1) launch_case_batch_t<1>(op, cs, map, nblocks, s);
     else if (storage == 2) launch_case_batch_t<2>(op, cs, map, nblocks, s);
     else launch_case_batch_t<0>(op, cs, map, nblocks, s);
+}
+
+void launch_macros(const Params &p, const void *A, long long n0, long long count, double *rho, double *u,
+                   hipStream_t s) {
+    const int grid = cdiv(count, 256);
+    if (p.storage == 0) k_macros<0><<<grid, 256, 0, s>>>(p, (const float *)A, n0, count, rho, u);
+    else if (p.storage == 1) k_macros<1><<<grid, 256, 0, s>>>(p, (const _Float16 *)A, n0, count, rho, u);
+    else k_macros<2><<<grid, 256, 0, s>>>(p, (const uint16_t *)A, n0, count, rho, u);
 }
 
 void launch_reset_counters(Counters *cnt, hipStream_t s) { k_reset_counters<<<1, 1, 0, s>>>(cnt); }

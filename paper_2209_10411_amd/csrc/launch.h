@@ -50,6 +50,9 @@ struct StepArgs {
 void launch_phase(const StepArgs &a);
 void launch_fill_i32(int32_t *a, long long n, int32_t v, hipStream_t s);
 void launch_fill_u8(uint8_t *a, long long n, uint8_t v, hipStream_t s);
+// Density [count] and velocity [count][3] (device, FP64) of the nodes from n0 on of the stored state A.
+void launch_macros(const Params &p, const void *A, long long n0, long long count, double *rho, double *u,
+                   hipStream_t s);
 void launch_reset_counters(Counters *cnt, hipStream_t s);
 // Re-flag: every node solid in own_old and fluid in own_new, listed for the
 // in-place refill and counted per body.

@@ -582,3 +582,38 @@ def test_kernel_timing_every_nth_step(mdl):
     sim.step(3)
     assert sim.timing_read()[1] == 0
     sim.close()
+
+
+@pytest.mark.parametrize("storage,size", [(workloads.STORE_F32, (33, 25, 40)), (workloads.STORE_F16, (24, 24, 40)),
+                                          (workloads.STORE_BF16, (27, 26, 41))])
+def test_fields_read_from_the_device(mdl, storage, size):
+    """Density and velocity are the moments of the populations read back
+    (19-term FP64 sums: 40 roundings of the largest term's sum), at sizes that
+    the read-out's turns do not divide; reading them leaves the run as it is."""
+    cfg = workloads.small_settling(n=24, nz=40, R=4.0, g=5e-4)
+    cfg.nx, cfg.ny, cfg.nz = size
+    cfg.particles[0].x = np.array([size[0] / 2, size[1] / 2, 0.6 * size[2]])
+    cfg.g_fluid = np.array([1e-6, 0.0, 2e-6])
+    cfg.storage = storage
+    print(f"fields storage {storage} size {size}", flush=True)
+    sim, twin = mdl.Simulation(cfg), mdl.Simulation(cfg)
+    for _ in range(3):
+        sim.step(3)
+        twin.step(3)
+        fl = sim.owner() < 0  # solid nodes hold no state (whatever the buffer held, NaN codes among it)
+        f = sim.populations()[:, fl]
+        rho, u = sim.macros()
+        rho, u = rho[fl], u[fl]
+        r = f.sum(0)
+        bound = 40 * 2.0 ** -53 * np.abs(f).sum(0)
+        assert np.all(np.abs(rho - r) <= bound)
+        for a, E in enumerate(oracle.lattice()[0].T):
+            v = (E[:, None] * f).sum(0) / r - 0.5 * cfg.g_fluid[a]
+            assert np.all(np.abs(u[:, a] - v) <= 2 * bound / r + 2.0 ** -52 * np.abs(v))
+    fl = sim.owner() < 0
+    assert np.array_equal(sim.owner(), twin.owner())
+    assert np.array_equal(sim.populations()[:, fl], twin.populations()[:, fl])
+    for k in ("x", "v", "F", "T"):
+        assert np.array_equal(sim.particles()[0][k], twin.particles()[0][k])
+    sim.close()
+    twin.close()
