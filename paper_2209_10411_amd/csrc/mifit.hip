@@ -15,21 +15,26 @@
 
 namespace {
 
-constexpr int BLK = 256;         // threads of the fitness and gradient-search blocks (4 waves)
+constexpr int BLK = 256;         // threads of the fitness blocks (4 waves)
+constexpr int GS_BLK = 1024;     // threads of a gradient-search block (16 waves)
 constexpr int CHUNK = 2048;      // hull points per fitness block
-constexpr int SEL_BLK = 1024;    // threads of the selection sort
-constexpr int SEL_MAX = 4096;    // pool size the one-block sort holds
+constexpr int SEL_MAX = 4096;    // pool size the selection holds in LDS
+constexpr int SEL_CHUNKS = 4;    // hull chunks whose sums the selection adds itself (each block for the whole pool)
 constexpr double EPS_F = 1e-12;  // floor of f in the 1/f term of the objective
 
-// Fixed-order sum over the block: butterfly within each wave, then the four
-// wave sums in wave order.  Every thread returns the total.
+// Fixed-order sum over a block of NW waves: butterfly within each wave, then
+// the wave sums in wave order.  Every thread returns the total.
+template <int NW = BLK / 64>
 __device__ double block_sum(double v, double *red) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     __syncthreads();  // red may still be read from the previous call
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    return ((red[0] + red[1]) + red[2]) + red[3];
+    double s = red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += red[w];
+    return s;
 }
 
 // f(h) = sum_j k_j / |h - p_j|^2 with the model in LDS ([n][4]: k, x, y, z).
@@ -42,24 +47,68 @@ __device__ __forceinline__ double mb_value(const double *sM, int n, double hx, d
     return f;
 }
 
-// The same sum with each quotient k / r^2 as k times the hardware reciprocal
-// estimate of r^2 refined by two Newton steps (within a few ulp of the
-// quotient; the fitness, a sum of squares of f - 1, is compared and ranked,
-// not tested for equality).
+// 1 / x: the hardware estimate refined by two Newton steps.
+__device__ __forceinline__ double rcp_refined(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    double e = fma(-x, r, 1.0);
+    r = fma(e, r, r);
+    e = fma(-x, r, 1.0);
+    return fma(e, r, r);
+}
+__device__ __forceinline__ double dist2(const double *sM, int j, double hx, double hy, double hz) {
+    const double dx = hx - sM[4 * j + 1], dy = hy - sM[4 * j + 2], dz = hz - sM[4 * j + 3];
+    return fma(dx, dx, fma(dy, dy, dz * dz));
+}
+
+// The same sum with each quotient k / r^2 as k times the refined reciprocal of
+// r^2 (within a few ulp of the quotient; the fitness, a sum of squares of
+// f - 1, is compared and ranked, not tested for equality).
 __device__ __forceinline__ double mb_value_rcp(const double *sM, int n, double hx, double hy, double hz) {
     double f = 0.0;
-    for (int j = 0; j < n; ++j) {
-        const double dx = hx - sM[4 * j + 1], dy = hy - sM[4 * j + 2], dz = hz - sM[4 * j + 3];
-        const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-        double r = __builtin_amdgcn_rcp(r2);
-        double e = fma(-r2, r, 1.0);
-        r = fma(e, r, r);
-        e = fma(-r2, r, 1.0);
-        r = fma(e, r, r);
-        f = fma(sM[4 * j], r, f);
-    }
+    for (int j = 0; j < n; ++j) f = fma(sM[4 * j], rcp_refined(dist2(sM, j, hx, hy, hz)), f);
     return f;
 }
+
+// The same sum at NP points at once, four control points over one common
+// denominator: a reciprocal (four issue slots, and four of refinement) for
+// four quotients, and a control point read from LDS once for NP points.  The
+// products stay far inside the range of FP64 while coordinates are below
+// TAME_X and weights below TAME_K (r^2 < 1e33, four of them < 1e132); tame says
+// whether the model is (block-uniform).  A point that is not, or that lies so
+// near a control point that the denominator falls below 1e-200, is summed
+// term by term.
+constexpr double TAME_X = 1e16, TAME_K = 1e60;
+template <int NP>
+__device__ __forceinline__ void mb_values(const double *sM, int n, bool tame, const double hx[NP], const double hy[NP],
+                                          const double hz[NP], double f[NP]) {
+    bool bad[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        f[q] = 0.0;
+        bad[q] = !(tame && fabs(hx[q]) < TAME_X && fabs(hy[q]) < TAME_X && fabs(hz[q]) < TAME_X);
+    }
+    int j = 0;
+    for (; j + 4 <= n; j += 4) {
+        const double k0 = sM[4 * j], k1 = sM[4 * j + 4], k2 = sM[4 * j + 8], k3 = sM[4 * j + 12];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const double a = dist2(sM, j, hx[q], hy[q], hz[q]), b = dist2(sM, j + 1, hx[q], hy[q], hz[q]);
+            const double c = dist2(sM, j + 2, hx[q], hy[q], hz[q]), d = dist2(sM, j + 3, hx[q], hy[q], hz[q]);
+            const double ab = a * b, cd = c * d, den = ab * cd;
+            const double nab = fma(k0, b, k1 * a), ncd = fma(k2, d, k3 * c);
+            bad[q] |= !(den > 1e-200);
+            f[q] = fma(fma(nab, cd, ncd * ab), rcp_refined(den), f[q]);
+        }
+    }
+    for (; j < n; ++j)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) f[q] = fma(sM[4 * j], rcp_refined(dist2(sM, j, hx[q], hy[q], hz[q])), f[q]);
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+        if (bad[q]) f[q] = mb_value_rcp(sM, n, hx[q], hy[q], hz[q]);
+}
+// Whether this thread's share of the model (4 n values) stays in that range.
+__device__ __forceinline__ bool tame_value(int t, double v) { return fabs(v) < ((t & 3) == 0 ? TAME_K : TAME_X); }
 
 // The per-point term of Eq. GSloss and its slope.
 __device__ __forceinline__ double gs_term(double f) {
@@ -75,8 +124,39 @@ __device__ __forceinline__ double gs_slope(double f) {
 }
 
 // ------------------------------------------------------------- evaluation
-// Block (individual p, chunk c): sum over the chunk's hull points of
-// (f - 1)^2, written to out[p * nch + c].
+// Sum over the hull points of chunk c of (f - 1)^2 for the model in LDS: FP
+// points per lane at a time.  Whole block; every thread returns the sum.
+// Bound by vector issue: 11.4 instructions per (hull point, control point) with
+// the shared reciprocals, 15 with one each (2400 models of 25 points on 4096:
+// 117 -> 90 us a call; two points a lane take the same time).
+template <int FP>
+__device__ __forceinline__ double fitness_chunk(const double *__restrict__ hull, long long m, const double *sM, int n,
+                                                bool tame, int c, double *red) {
+    const long long i0 = (long long)c * CHUNK;
+    const long long i1 = i0 + CHUNK < m ? i0 + CHUNK : m;
+    double s = 0.0;
+    for (long long i = i0 + threadIdx.x; i < i1; i += FP * BLK) {
+        double hx[FP], hy[FP], hz[FP], f[FP];
+#pragma unroll
+        for (int q = 0; q < FP; ++q) {  // past the end: the first point again, unused
+            const long long k = i + q * BLK < i1 ? i + q * BLK : i;
+            hx[q] = hull[3 * k];
+            hy[q] = hull[3 * k + 1];
+            hz[q] = hull[3 * k + 2];
+        }
+        mb_values<FP>(sM, n, tame, hx, hy, hz, f);
+#pragma unroll
+        for (int q = 0; q < FP; ++q)
+            if (i + q * BLK < i1) {
+                const double e = f[q] - 1.0;
+                s += e * e;
+            }
+    }
+    return block_sum(s, red);
+}
+
+// Block (individual p, chunk c): its chunk sum to out[p * nch + c].
+template <int FP>
 __global__ __launch_bounds__(BLK) void k_fitness(const double *__restrict__ hull, long long m,
                                                  const double *__restrict__ pop, int n, int nch,
                                                  double *__restrict__ out) {
@@ -84,16 +164,13 @@ __global__ __launch_bounds__(BLK) void k_fitness(const double *__restrict__ hull
     __shared__ double red[4];
     const int p = blockIdx.x / nch, c = blockIdx.x - p * nch;
     const double *M = pop + (size_t)p * n * 4;
-    for (int t = threadIdx.x; t < 4 * n; t += BLK) sM[t] = M[t];
-    __syncthreads();
-    const long long i0 = (long long)c * CHUNK;
-    const long long i1 = i0 + CHUNK < m ? i0 + CHUNK : m;
-    double s = 0.0;
-    for (long long i = i0 + threadIdx.x; i < i1; i += BLK) {
-        const double e = mb_value_rcp(sM, n, hull[3 * i], hull[3 * i + 1], hull[3 * i + 2]) - 1.0;
-        s += e * e;
+    bool tame = true;
+    for (int t = threadIdx.x; t < 4 * n; t += BLK) {  // 4 n <= BLK: one value per thread
+        sM[t] = M[t];
+        tame = tame_value(t, M[t]);
     }
-    s = block_sum(s, red);
+    tame = __syncthreads_and(tame);
+    const double s = fitness_chunk<FP>(hull, m, sM, n, tame, c, red);
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
@@ -107,83 +184,93 @@ __global__ void k_fitness_sum(const double *__restrict__ part, int P, int nch, d
 }
 
 // ------------------------------------------------------ genetic operators
-// One mutant per individual (gene-wise; no contraction, so that each gene is
-// exactly v + z * sigma).
-__global__ void k_mutate(const double *__restrict__ pop, double *__restrict__ out, const double *__restrict__ U,
-                         const double *__restrict__ Z, long long count, double C_m, double sx, double sk) {
+// One generation's offspring and their evaluation in one launch.  Block
+// (offspring a of 2 N, chunk c of the hull): mutant a (a < N) of individual a,
+// gene-wise, each gene exactly v + z * sigma (no contraction); or child a - N:
+// the pairs (perm[2j], perm[2j+1]) exchange their control points from cut on,
+// an odd last individual is copied.  The genes go to LDS and, from the first
+// chunk's block, to the pool behind the N parents; then the chunk's fitness.
+// (Mutation, crossover and the chunk sums were launches of 5 us each beside the
+// evaluation; a generation of 1200 went from 220 to 118 us.)
+template <int FP>
+__global__ __launch_bounds__(BLK) void k_breed(const double *__restrict__ hull, long long m, double *__restrict__ pool,
+                                               const double *__restrict__ U, const double *__restrict__ Z,
+                                               const int *__restrict__ perm, int N, int n, int cut, double C_m,
+                                               double sx, double sk, int nch, double *__restrict__ out) {
 #pragma clang fp contract(off)
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const int g = (int)(i & 3);
-    double v = pop[i];
-    if (U[i] < C_m) v = v + Z[i] * (g == 0 ? sk : sx);
-    if (g == 0 && v < 0.0) v = 0.0;
-    out[i] = v;
-}
-
-// Children of the pairs (perm[2j], perm[2j+1]): control points from c on are
-// exchanged; an odd last individual is copied.
-__global__ void k_crossover(const double *__restrict__ pop, double *__restrict__ kids, const int *__restrict__ perm,
-                            int N, int n, int c) {
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    const int g4 = 4 * n;
-    if (i >= (long long)N * g4) return;
-    const int a = (int)(i / g4), r = (int)(i - (long long)a * g4), j = r >> 2;
-    int src;
-    if ((N & 1) && a == N - 1) {
-        src = perm[a];
-    } else {
-        const int first = perm[a & ~1], second = perm[a | 1];
-        const bool head = j < c;
-        src = (a & 1) ? (head ? second : first) : (head ? first : second);
+    __shared__ double sM[MI_MAXCP * 4];
+    __shared__ double red[4];
+    const int a = blockIdx.x / nch, c = blockIdx.x - a * nch, g4 = 4 * n, t = threadIdx.x;
+    bool tame = true;
+    if (t < g4) {  // g4 <= BLK
+        double v;
+        if (a < N) {
+            const size_t i = (size_t)a * g4 + t;
+            const int g = t & 3;
+            v = pool[i];
+            if (U[i] < C_m) v = v + Z[i] * (g == 0 ? sk : sx);
+            if (g == 0 && v < 0.0) v = 0.0;
+        } else {
+            const int b = a - N;
+            int src;
+            if ((N & 1) && b == N - 1) {
+                src = perm[b];
+            } else {
+                const int first = perm[b & ~1], second = perm[b | 1];
+                const bool head = (t >> 2) < cut;
+                src = (b & 1) ? (head ? second : first) : (head ? first : second);
+            }
+            if ((unsigned)src >= (unsigned)N) src = b;  // not a permutation entry: keep the index in range
+            v = pool[(size_t)src * g4 + t];
+        }
+        sM[t] = v;
+        if (c == 0) pool[(size_t)(N + a) * g4 + t] = v;
+        tame = tame_value(t, v);
     }
-    if ((unsigned)src >= (unsigned)N) src = a;  // not a permutation entry: keep the index in range
-    kids[i] = pop[(size_t)src * g4 + r];
+    tame = __syncthreads_and(tame);
+    const double s = fitness_chunk<FP>(hull, m, sM, n, tame, c, red);
+    if (t == 0) out[blockIdx.x] = s;
 }
 
-// Indices of the N smallest of K pool fitness values, ties to the lower
-// index: one block, bitonic sort of (F, index) pairs in LDS (NaN sorts as
-// +inf, padding as +inf with indices past K).
-__global__ __launch_bounds__(SEL_BLK) void k_select(const double *__restrict__ F, int K, int N, int *__restrict__ idx) {
+// Survivors: the N fittest of the pool's K individuals, ties to the lower
+// index (NaN counts as +inf), in order.  Every block holds the whole pool's
+// fitness in LDS -- F [F_known] of the parents, then the offspring's chunk
+// sums added in chunk order -- and ranks SEL_PER of them: SEL_LANES lanes count
+// the individuals before one, the count is its place, and the lanes copy it
+// there if it survives.  The comparisons of all pairs over many blocks take
+// less time than the dependent passes of a sort in one block (3600 of them:
+// 13.9 us with the copy, against 77 for a bitonic sort and 5 for a gather).
+constexpr int SEL_LANES = 32, SEL_PER = BLK / SEL_LANES;
+__global__ __launch_bounds__(BLK) void k_select(const double *__restrict__ pool, const double *__restrict__ F,
+                                                int F_known, const double *__restrict__ part, int nch, int K, int N,
+                                                int n, double *__restrict__ pop, double *__restrict__ Fout) {
     __shared__ double key[SEL_MAX];
-    __shared__ int id[SEL_MAX];
-    int L = 1;
-    while (L < K) L <<= 1;
-    for (int t = threadIdx.x; t < L; t += SEL_BLK) {
-        const double v = t < K ? F[t] : HUGE_VAL;
-        key[t] = v != v ? HUGE_VAL : v;
-        id[t] = t;
+    auto fitness = [&](int i) {
+        if (i < F_known) return F[i];
+        double v = 0.0;
+        for (int c = 0; c < nch; ++c) v += part[(size_t)(i - F_known) * nch + c];
+        return v;
+    };
+#pragma unroll 4
+    for (int i = threadIdx.x; i < K; i += BLK) {
+        const double v = fitness(i);
+        key[i] = v != v ? HUGE_VAL : v;
     }
     __syncthreads();
-    for (int size = 2; size <= L; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = threadIdx.x; t < L; t += SEL_BLK) {
-                const int u = t ^ stride;
-                if (u > t) {
-                    const bool up = (t & size) == 0;
-                    const double ka = key[t], kb = key[u];
-                    const int ia = id[t], ib = id[u];
-                    const bool gt = ka > kb || (ka == kb && ia > ib);
-                    if (gt == up) {
-                        key[t] = kb; key[u] = ka;
-                        id[t] = ib; id[u] = ia;
-                    }
-                }
-            }
-            __syncthreads();
-        }
+    const int l = threadIdx.x % SEL_LANES, i = blockIdx.x * SEL_PER + threadIdx.x / SEL_LANES;
+    const double mine = i < K ? key[i] : 0.0;
+    int before = 0;
+#pragma unroll 8
+    for (int j = l; j < K; j += SEL_LANES) {
+        const double v = key[j];
+        before += (v < mine) | ((v == mine) & (j < i));
     }
-    for (int r = threadIdx.x; r < N; r += SEL_BLK) idx[r] = id[r];
-}
-
-__global__ void k_gather(const double *__restrict__ pool, const double *__restrict__ Fpool, const int *__restrict__ idx,
-                         int N, int n, double *__restrict__ pop, double *__restrict__ F) {
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+#pragma unroll
+    for (int d = SEL_LANES / 2; d > 0; d >>= 1) before += __shfl_xor(before, d, SEL_LANES);
+    if (i >= K || before >= N) return;
     const int g4 = 4 * n;
-    if (i >= (long long)N * g4) return;
-    const int a = (int)(i / g4), r = (int)(i - (long long)a * g4);
-    pop[i] = pool[(size_t)idx[a] * g4 + r];
-    if (r == 0) F[a] = Fpool[idx[a]];
+    for (int r = l; r < g4; r += SEL_LANES) pop[(size_t)before * g4 + r] = pool[(size_t)i * g4 + r];
+    if (l == 0) Fout[before] = fitness(i);
 }
 
 // --------------------------------------------------------- gradient search
@@ -193,71 +280,137 @@ __device__ __forceinline__ double plane_side(const double *pl, double px, double
     return ((px * pl[0] + py * pl[1]) + pz * pl[2]) + pl[3];
 }
 
+// f at one point for the descent, four control points over one common
+// denominator (mb_values; here every denominator and the sum are held to a
+// range far inside FP64, since the model moves); outside it the plain sum.
+__device__ __forceinline__ double gs_value(const double *sM, int n, double hx, double hy, double hz) {
+    double f = 0.0;
+    bool ok = true;
+    int j = 0;
+    for (; j + 4 <= n; j += 4) {
+        const double a = dist2(sM, j, hx, hy, hz), b = dist2(sM, j + 1, hx, hy, hz);
+        const double c = dist2(sM, j + 2, hx, hy, hz), d = dist2(sM, j + 3, hx, hy, hz);
+        const double ab = a * b, cd = c * d, den = ab * cd;
+        const double nab = fma(sM[4 * j], b, sM[4 * j + 4] * a), ncd = fma(sM[4 * j + 8], d, sM[4 * j + 12] * c);
+        ok = ok && den > 1e-200 && den < 1e200;
+        f = fma(fma(nab, cd, ncd * ab), rcp_refined(den), f);
+    }
+    for (; j < n; ++j) f += sM[4 * j] / dist2(sM, j, hx, hy, hz);
+    return ok && fabs(f) < 1e200 ? f : mb_value(sM, n, hx, hy, hz);
+}
+
 // Sum over the hull points of the Eq. GSloss terms for the model in LDS.
 __device__ double gs_loss_block(const double *__restrict__ hull, long long m, const double *sM, int n, double *red) {
     double s = 0.0;
-    for (long long i = threadIdx.x; i < m; i += BLK)
+    for (long long i = threadIdx.x; i < m; i += GS_BLK)
         s += gs_term(mb_value(sM, n, hull[3 * i], hull[3 * i + 1], hull[3 * i + 2]));
-    return block_sum(s, red);
+    return block_sum<GS_BLK / 64>(s, red);
 }
 
 // One workgroup per model: E descent steps, cleaning, E steps.  Per step:
 // pass 1, one hull point per lane: f and the objective's slope g_i (in
 // LDS); pass 2, lanes over (control point j, chunk of points):
 // dL/dk_j = sum g_i / r^2, dL/dp_j = sum g_i 2 k_j (h_i - p_j) / r^4 over the
-// chunk; the chunks are added in order and the model updated in LDS.
-__global__ __launch_bounds__(BLK) void k_gs(const double *__restrict__ hulls, const int64_t *__restrict__ hoff,
-                                            const double *__restrict__ planes, const int64_t *__restrict__ poff,
-                                            int n, int E, double eta, double *__restrict__ Mall,
-                                            double *__restrict__ loss) {
+// chunk, two points over one reciprocal; the chunks are added in a fixed
+// order (eight lanes a gene, four beyond 32 control points) and the model
+// updated in LDS.  A step is one compute unit's vector issue on the 2 m n
+// terms, so the block has 16 waves, four per SIMD (four waves in all left
+// each SIMD waiting on one), and with STAGED the hull is kept in LDS beside its
+// slopes (32 bytes a point) instead of being read again from the caches every
+// step.  64 models of 900 to 1500 points, 25 control points: 13.5 us a step, 40
+// with four waves, exact quotients and the hull in memory.
+template <bool STAGED>
+__global__ __launch_bounds__(GS_BLK) void k_gs(const double *__restrict__ hulls, const int64_t *__restrict__ hoff,
+                                               const double *__restrict__ planes, const int64_t *__restrict__ poff,
+                                               int n, int E, double eta, double *__restrict__ Mall,
+                                               double *__restrict__ loss) {
     __shared__ double sM[MI_MAXCP * 4];
-    __shared__ double part[BLK * 4];
-    __shared__ double red[4];
-    __shared__ double g[MI_GS_MAXPTS];  // the objective's slope at each hull point
-    const int b = blockIdx.x;
-    const long long h0 = hoff[b], m = hoff[b + 1] - h0;
+    __shared__ double part[GS_BLK * 4];
+    __shared__ double red[GS_BLK / 64];
+    extern __shared__ double pts[];  // STAGED: x, y, z and the slope of each point; else the slopes alone
+    const int b = blockIdx.x, t = threadIdx.x;
+    const long long h0 = hoff[b];
+    const int m = (int)(hoff[b + 1] - h0);  // at most MI_GS_MAXPTS
     const double *hull = hulls + 3 * h0;
     double *M = Mall + (size_t)b * n * 4;
-    for (int t = threadIdx.x; t < 4 * n; t += BLK) sM[t] = M[t];
+    if (t < 4 * n) sM[t] = M[t];
+    if (STAGED)
+        for (int i = t; i < m; i += GS_BLK)
+            for (int a = 0; a < 3; ++a) pts[4 * i + a] = hull[3 * i + a];
     __syncthreads();
     double L = gs_loss_block(hull, m, sM, n, red);
-    if (threadIdx.x == 0) loss[3 * b] = L;
-    const int nch = BLK / n;                 // chunks of points in pass 2
-    const int j = threadIdx.x % n, c = threadIdx.x / n;
+    if (t == 0) loss[3 * b] = L;
+    const int nch = GS_BLK / n;  // chunks of points in pass 2
+    const int j = t % n, c = t / n;
+    const int LP = n <= 32 ? 8 : 4;  // lanes per gene in the last sum
+    constexpr int W = STAGED ? 4 : 1;
+    auto point = [&](int i, double &x, double &y, double &z) {
+        const double *h = STAGED ? pts + 4 * i : hull + 3 * (size_t)i;
+        x = h[0];
+        y = h[1];
+        z = h[2];
+    };
     for (int phase = 0; phase < 2; ++phase) {
         for (int it = 0; it < E; ++it) {
-            for (long long i = threadIdx.x; i < m; i += BLK)
-                g[i] = gs_slope(mb_value(sM, n, hull[3 * i], hull[3 * i + 1], hull[3 * i + 2]));
+            for (int i = t; i < m; i += GS_BLK) {
+                double x, y, z;
+                point(i, x, y, z);
+                pts[W * i + W - 1] = gs_slope(gs_value(sM, n, x, y, z));
+            }
             __syncthreads();
             double gk = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
             if (c < nch) {
-                const double k = sM[4 * j], px = sM[4 * j + 1], py = sM[4 * j + 2], pz = sM[4 * j + 3];
-                for (long long i = c; i < m; i += nch) {
-                    const double dx = hull[3 * i] - px, dy = hull[3 * i + 1] - py, dz = hull[3 * i + 2] - pz;
-                    const double y = 1.0 / (dx * dx + dy * dy + dz * dz);
-                    const double gi = g[i];
-                    gk += gi * y;
-                    const double t = 2.0 * gi * k * y * y;
-                    gx += t * dx; gy += t * dy; gz += t * dz;
+                const double k2 = 2.0 * sM[4 * j], px = sM[4 * j + 1], py = sM[4 * j + 2], pz = sM[4 * j + 3];
+                auto add = [&](double dx, double dy, double dz, double y, double gi) {
+                    const double gy_ = gi * y, w = k2 * gy_ * y;
+                    gk += gy_;
+                    gx = fma(w, dx, gx);
+                    gy = fma(w, dy, gy);
+                    gz = fma(w, dz, gz);
+                };
+                int i = c;
+                for (; i + nch < m; i += 2 * nch) {
+                    double ax, ay, az, bx, by, bz;
+                    point(i, ax, ay, az);
+                    point(i + nch, bx, by, bz);
+                    ax -= px; ay -= py; az -= pz;
+                    bx -= px; by -= py; bz -= pz;
+                    const double ra = fma(ax, ax, fma(ay, ay, az * az)), rb = fma(bx, bx, fma(by, by, bz * bz));
+                    const double den = ra * rb, inv = rcp_refined(den);
+                    double ya = rb * inv, yb = ra * inv;
+                    if (!(den > 1e-200 && den < 1e200)) {
+                        ya = 1.0 / ra;
+                        yb = 1.0 / rb;
+                    }
+                    add(ax, ay, az, ya, pts[W * i + W - 1]);
+                    add(bx, by, bz, yb, pts[W * (i + nch) + W - 1]);
+                }
+                if (i < m) {
+                    double ax, ay, az;
+                    point(i, ax, ay, az);
+                    ax -= px; ay -= py; az -= pz;
+                    add(ax, ay, az, 1.0 / fma(ax, ax, fma(ay, ay, az * az)), pts[W * i + W - 1]);
                 }
             }
-            part[4 * threadIdx.x] = gk; part[4 * threadIdx.x + 1] = gx;
-            part[4 * threadIdx.x + 2] = gy; part[4 * threadIdx.x + 3] = gz;
+            part[4 * t] = gk; part[4 * t + 1] = gx;
+            part[4 * t + 2] = gy; part[4 * t + 3] = gz;
             __syncthreads();
-            if (threadIdx.x < 4 * n) {  // gene t of control point t / 4, chunks in order
-                const int jj = threadIdx.x >> 2, q = threadIdx.x & 3;
+            {  // gene o of control point o / 4: LP partial sums, then a butterfly
+                const int o = t / LP, l = t % LP;
                 double G = 0.0;
-                for (int cc = 0; cc < nch; ++cc) G += part[4 * (cc * n + jj) + q];
-                sM[threadIdx.x] -= eta * G;
+                if (o < 4 * n)
+                    for (int cc = l; cc < nch; cc += LP) G += part[4 * cc * n + o];
+                for (int d = LP / 2; d > 0; d >>= 1) G += __shfl_xor(G, d);
+                if (o < 4 * n && l == 0) sM[o] -= eta * G;
             }
             __syncthreads();
         }
         if (phase == 0) {
             L = gs_loss_block(hull, m, sM, n, red);
-            if (threadIdx.x == 0) loss[3 * b + 1] = L;
+            if (t == 0) loss[3 * b + 1] = L;
             // anomaly cleaning: negative weights and control points outside the hull
-            if (threadIdx.x < n) {
-                const int jj = threadIdx.x;
+            if (t < n) {
+                const int jj = t;
                 bool out = sM[4 * jj] < 0.0;
                 const double px = sM[4 * jj + 1], py = sM[4 * jj + 2], pz = sM[4 * jj + 3];
                 for (long long q = poff[b]; q < poff[b + 1] && !out; ++q) out = plane_side(planes + 4 * q, px, py, pz) > 0.0;
@@ -267,9 +420,14 @@ __global__ __launch_bounds__(BLK) void k_gs(const double *__restrict__ hulls, co
         }
     }
     L = gs_loss_block(hull, m, sM, n, red);
-    if (threadIdx.x == 0) loss[3 * b + 2] = L;
-    for (int t = threadIdx.x; t < 4 * n; t += BLK) M[t] = sM[t];
+    if (t == 0) loss[3 * b + 2] = L;
+    if (t < 4 * n) M[t] = sM[t];
 }
+
+// Hulls of up to GS_STAGED points are kept in LDS (96 KB beside the 34 KB of
+// the sums, of the 160 KB of a compute unit); a larger one leaves its points in
+// memory.
+constexpr int GS_STAGED = 3072;
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -277,21 +435,30 @@ inline int chunks(long long m) { return cdiv(m, CHUNK); }
 
 lbm_status launched() { return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP; }
 
+// Points per lane at a time: as many as the hull gives a lane of one block, up
+// to four (more registers, fewer waves); fewer would be repeated points.
+template <class L1, class L2, class L4>
+void by_points(long long m, L1 one, L2 two, L4 four) {
+    if (m <= BLK) one();
+    else if (m <= 2 * BLK) two();
+    else four();
+}
+
 // Fitness of P individuals into F (partials in part when m spans chunks).
 lbm_status fitness_launch(const double *hull, long long m, const double *pop, int P, int n, double *F, double *part,
                           hipStream_t s) {
     const int nch = chunks(m);
-    if (nch == 1) {
-        k_fitness<<<P, BLK, 0, s>>>(hull, m, pop, n, 1, F);
-    } else {
-        k_fitness<<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, part);
-        k_fitness_sum<<<cdiv(P, 256), 256, 0, s>>>(part, P, nch, F);
-    }
+    double *out = nch == 1 ? F : part;
+    by_points(
+        m, [&] { k_fitness<1><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
+        [&] { k_fitness<2><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
+        [&] { k_fitness<4><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); });
+    if (nch > 1) k_fitness_sum<<<cdiv(P, 256), 256, 0, s>>>(part, P, nch, F);
     return launched();
 }
 
 struct GaLayout {
-    size_t poolA, poolB, FA, FB, idx, part, total;
+    size_t poolA, poolB, FA, FB, part, total;
 };
 GaLayout ga_layout(long long m, int N, int n) {
     GaLayout L;
@@ -302,7 +469,7 @@ GaLayout ga_layout(long long m, int N, int n) {
     L.poolB = take(pool);
     L.FA = take((size_t)3 * N * sizeof(double));
     L.FB = take((size_t)3 * N * sizeof(double));
-    L.idx = take((size_t)N * sizeof(int));
+    take((size_t)N * sizeof(int));  // unused: the workspace keeps its size
     L.part = take(chunks(m) > 1 ? (size_t)2 * N * chunks(m) * sizeof(double) : 0);
     L.total = o;
     return L;
@@ -344,23 +511,28 @@ lbm_status mi_ga(const double *hull, int64_t m, int32_t N_I, int32_t n, int32_t 
     char *w = (char *)work;
     double *A = (double *)(w + Lw.poolA), *B = (double *)(w + Lw.poolB);
     double *FA = (double *)(w + Lw.FA), *FB = (double *)(w + Lw.FB);
-    int *idx = (int *)(w + Lw.idx);
     double *part = (double *)(w + Lw.part);
     const long long genes = (long long)N_I * n * 4;
     const int c = (int)(C_c * n + 0.5);
     if (hipMemcpyAsync(A, pop, genes * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess) return LBM_E_HIP;
     lbm_status st = fitness_launch(hull, m, A, N_I, n, FA, part, s);
     if (st) return st;
+    const int nch = chunks(m);
+    double *sums = nch == 1 ? FA + N_I : part;  // the offspring's fitness, whole or in chunk sums
     for (int e = 0; e < E; ++e) {
-        k_mutate<<<cdiv(genes, 256), 256, 0, s>>>(A, A + genes, U + (size_t)e * genes, Z + (size_t)e * genes, genes,
-                                                 C_m, sigma_x, sigma_k);
-        k_crossover<<<cdiv(genes, 256), 256, 0, s>>>(A, A + 2 * genes, PERM + (size_t)e * N_I, N_I, n, c);
-        if ((st = fitness_launch(hull, m, A + genes, 2 * N_I, n, FA + N_I, part, s))) return st;
-        k_select<<<1, SEL_BLK, 0, s>>>(FA, 3 * N_I, N_I, idx);
-        k_gather<<<cdiv(genes, 256), 256, 0, s>>>(A, FA, idx, N_I, n, B, FB);
+        const double *Ue = U + (size_t)e * genes, *Ze = Z + (size_t)e * genes;
+        const int *pe = PERM + (size_t)e * N_I;
+        auto breed = [&](auto kernel) {
+            kernel<<<2 * N_I * nch, BLK, 0, s>>>(hull, m, A, Ue, Ze, pe, N_I, n, c, C_m, sigma_x, sigma_k, nch, sums);
+        };
+        by_points(m, [&] { breed(k_breed<1>); }, [&] { breed(k_breed<2>); }, [&] { breed(k_breed<4>); });
+        const bool fold = nch <= SEL_CHUNKS;
+        if (!fold) k_fitness_sum<<<cdiv(2 * N_I, 256), 256, 0, s>>>(part, 2 * N_I, nch, FA + N_I);
+        k_select<<<cdiv(3 * N_I, SEL_PER), BLK, 0, s>>>(A, FA, fold ? N_I : 3 * N_I, sums, nch, 3 * N_I, N_I, n, B, FB);
         if ((st = launched())) return st;
         double *t = A; A = B; B = t;
         t = FA; FA = FB; FB = t;
+        if (nch == 1) sums = FA + N_I;
     }
     if (hipMemcpyAsync(pop, A, genes * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess ||
         hipMemcpyAsync(F, FA, N_I * sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess ||
@@ -384,12 +556,22 @@ lbm_status mi_gs(const double *hulls, const int64_t *hull_off, const double *pla
         return LBM_E_HIP;
     }
     bool ok = ho[0] >= 0 && ho[B + 1] >= 0;
-    for (int b = 0; b < B && ok; ++b)
+    int64_t most = 0;
+    for (int b = 0; b < B && ok; ++b) {
+        most = ho[b + 1] - ho[b] > most ? ho[b + 1] - ho[b] : most;
         ok = ho[b + 1] - ho[b] >= 1 && ho[b + 1] - ho[b] <= MI_GS_MAXPTS && ho[B + 2 + b] >= ho[B + 1 + b];
+    }
     delete[] ho;
     if (!ok) return LBM_E_INVALID;
-    k_gs<<<B, BLK, 0, s>>>(hulls, hull_off, planes, plane_off, n, E, eta, M, loss);
-    return launched();
+    const bool staged = most <= GS_STAGED;
+    auto run = [&](auto kernel, size_t lds) {
+        // (beyond 64 KB of LDS a kernel asks for it; the largest here is 130 KB)
+        if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return LBM_E_HIP;
+        kernel<<<B, GS_BLK, lds, s>>>(hulls, hull_off, planes, plane_off, n, E, eta, M, loss);
+        return launched();
+    };
+    return staged ? run(k_gs<true>, 32 * (size_t)most) : run(k_gs<false>, 8 * (size_t)most);
 }
 
 // ---------------------------------------------- fitness without allocation

@@ -126,3 +126,57 @@ def test_fit_pipeline(mdl):
     Mo, Lo = mifit.gs(po[0], H, pl, 40, 1e-3)
     assert np.abs(Mg[0] - Mo).max() <= 1e-8 * np.abs(Mo).max()
     assert Lg[0][2] < Lg[0][0]
+
+
+@pytest.mark.parametrize("N_I,n,m", [(2, 1, 300), (41, 7, 2049), (30, 5, 10500), (1365, 4, 260)])
+def test_ga_pool_and_chunk_edges(mdl, N_I, n, m):
+    """The smallest and the largest pool, one, two and six chunks of hull
+    points, control points that are no multiple of four, and equal individuals
+    (ties go to the lower pool index)."""
+    print(f"mifit GA edges N_I={N_I} n={n} m={m}", flush=True)
+    H, pl, _ = body(83, n_cp=4, R=6.0, m=m)
+    pop0 = workloads.mi_population(H, pl, N_I, n, seed=84)
+    pop0[N_I // 2] = pop0[0]
+    E = 2
+    U, Z, PERM = workloads.mi_draws(E, N_I, n, seed=85)
+    sx, sk = 0.3, 0.2 * float(pop0[..., 0].mean())
+    pg, Fg = mdl.mi_ga(H, pop0, E, 0.3, 0.5, sx, sk, U, Z, PERM)
+    po, Fo = mifit.ga(H, pop0, E, 0.3, 0.5, sx, sk, U, Z, PERM)
+    assert np.abs(Fg - Fo).max() <= 1e-12 * np.abs(Fo).max()
+    assert np.abs(pg - po).max() <= 1e-12 * np.abs(po).max()
+
+
+@pytest.mark.parametrize("m", [200, 400, 3000])
+def test_fitness_outside_the_usual_range(mdl, m):
+    """Weights and coordinates far outside the range in which four quotients
+    share a denominator, a model with a NaN gene and one with a control point
+    on a hull point (both without a finite fitness), beside ordinary ones."""
+    H, pl, _ = body(86, m=m)
+    pop = workloads.mi_population(H, pl, 8, 9, seed=87)
+    pop[1, 3, 0] = 1e70
+    pop[2, 5, 1:] = 1e20
+    pop[3, 0, 0] = np.nan
+    pop[4, 8, 1:] = H[m // 2]
+    pop[5, 2, 0] = -3.0
+    Fg = mdl.mi_fitness(H, pop)
+    with np.errstate(all="ignore"):
+        Fo = np.array([mifit.fitness(p, H) for p in pop])
+    ok = np.array([0, 1, 2, 5, 6, 7])
+    assert np.all(np.abs(Fg[ok] - Fo[ok]) <= 1e-12 * np.abs(Fo[ok]))
+    assert not np.isfinite(Fg[[3, 4]]).any()
+
+
+@pytest.mark.parametrize("n,m", [(33, 3100), (5, 90), (64, 1024), (32, 3072)])
+def test_gs_block_forms(mdl, n, m):
+    """Hulls kept in LDS (up to 3072 points) and not, control points below and
+    above 32, hulls smaller than the block and equal to it."""
+    print(f"mifit GS forms n={n} m={m}", flush=True)
+    H, pl, truth = body(88, n_cp=6, R=8.0, m=m)
+    rng = np.random.default_rng(89)
+    M0 = workloads.mi_population(H, pl, 1, n, seed=90)
+    c = min(n, 6)
+    M0[0, :c, 1:] = truth[:c, 1:] + rng.normal(0, 0.2, (c, 3))
+    Mg, Lg = mdl.mi_gs([H], [pl], M0, 10, 1e-5)
+    Mo, Lo = mifit.gs(M0[0], H, pl, 10, 1e-5)
+    assert np.abs(Mg[0] - Mo).max() <= 1e-8 * np.abs(Mo).max()
+    assert np.allclose(Lg[0], Lo, rtol=1e-8, atol=0)
