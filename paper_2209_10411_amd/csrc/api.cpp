@@ -1260,11 +1260,11 @@ lbm_status mlp_train(void *dev_feat, void *dev_target, int64_t n, const char *hp
     for (int e = 0; e < ne; ++e)
         for (int64_t a = 0; a < n; a += bs) {
             const int m = (int)std::min<int64_t>(bs, n - a);
-            launch_mlp_loss_grad(b, (const char *)dev_feat + (size_t)a * MLP_IN * xb,
-                                 (const float *)dev_target + (size_t)a * MLP_OUT, m, pr, st);
             ++t;
             const double bc1 = 1.0 - std::pow(b1, (double)t), bc2 = 1.0 - std::pow(b2, (double)t);
-            launch_mlp_adam(b, (float)lr, (float)b1, (float)b2, (float)eps, (float)bc1, (float)bc2, st);
+            launch_mlp_adam_step(b, (const char *)dev_feat + (size_t)a * MLP_IN * xb,
+                                 (const float *)dev_target + (size_t)a * MLP_OUT, m, pr, (float)lr, (float)b1, (float)b2,
+                                 (float)eps, (float)bc1, (float)bc2, st);
         }
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(b.t, &t, 8, hipMemcpyHostToDevice, st));

@@ -190,20 +190,20 @@ struct MlpBlob {
     float *theta, *m, *v;  // FP32 master parameters and Adam moments [P]
     _Float16 *w16;         // FP16 copy of the parameters [P]
     long long *t;          // Adam step count
-    float *h1, *h2;        // [B][64] activations (FP16 or FP32 storage)
-    float *out, *dout;     // [B][4]
-    float *dz1, *dz2;      // [B][64]
+    float *h1, *h2;        // [B][64] activations (FP16 or FP32 storage); h1 also the slices' gradients [16][P]
+    float *out;            // [B][4]
+    float *sq;             // [B][4] squared errors
     float *g;              // [P] gradient
     float *loss;           // [1]
-    float *part;           // [16][88][64] weight-gradient slices
 };
 size_t mlp_blob_bytes();
 MlpBlob mlp_blob(void *base);
 void launch_mlp_init(const MlpBlob &b, hipStream_t s);  // m = v = 0, t = 0, w16 = theta
 void launch_mlp_forward(const MlpBlob &b, const void *X, int n, int precision, hipStream_t s);
 void launch_mlp_loss_grad(const MlpBlob &b, const void *X, const float *T, int n, int precision, hipStream_t s);
-void launch_mlp_adam(const MlpBlob &b, float lr, float beta1, float beta2, float eps, float bc1, float bc2,
-                     hipStream_t s);
+// One Adam step on the gradient of the n samples (b.g and b.loss are left as they are).
+void launch_mlp_adam_step(const MlpBlob &b, const void *X, const float *T, int n, int precision, float lr, float beta1,
+                          float beta2, float eps, float bc1, float bc2, hipStream_t s);
 void launch_mlp_collect(const Params &p, const DevParticle *P, const float *body, const uint32_t *l_node,
                         const uint32_t *l_do, const double *l_q, int n, _Float16 *feat, float *target,
                         hipStream_t s);

@@ -339,3 +339,19 @@ def test_warm_started_contacts_match_plain(mdl, trained):
         assert np.abs(a["v"] - b["v"]).max() < 1e-9
     plain.close()
     warm.close()
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 250, 257, 1000])
+def test_gradient_of_ragged_batches(mdl, n):
+    """Batches smaller than the sixteen slices, slices of one tile and a part
+    of one, and of several tiles (FP32 form, the bound of the test above)."""
+    import torch
+    rng = np.random.default_rng(300 + n)
+    X, T = rand_batch(rng, n)
+    theta = params(9)
+    net = mdl.Mlp(theta.astype(np.float32))
+    th, Xr, Tr = theta.astype(np.float32).astype(np.float64), X.astype(np.float32), T.astype(np.float32)
+    g, loss = net.grad(torch.tensor(Xr, device="cuda:0"), torch.tensor(Tr, device="cuda:0"), 1)
+    gr = omlp.grad(th, Xr.astype(np.float64), Tr.astype(np.float64))
+    assert np.abs(g - gr).max() <= 1e-5 * np.abs(gr).max()
+    assert loss == pytest.approx(omlp.loss(th, Xr.astype(np.float64), Tr.astype(np.float64)), rel=1e-5)
