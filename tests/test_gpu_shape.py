@@ -98,3 +98,34 @@ def test_designed_particles_of_the_dkt_table(mdl):
         assert abs(d["CSF"] - csf) < 3e-3
         assert abs(d["Phi"] - phi) < 2e-3
         assert abs(d["d_n"] / d["d_s"] - dnds) < 2e-3
+
+
+@pytest.mark.parametrize("n,R,h", [(3, 6.0, 0.9), (20, 4.0, 0.31), (64, 5.0, 0.4), (2, 3.0, 2.6)])
+def test_patch_and_segment_edges(mdl, n, R, h):
+    """Grids of a few cells (one patch), of several patches of 15 and segments
+    of 32 cells with remainders, the most control points, a coarse grid."""
+    cp, k = workloads.random_body(np.random.Generator(np.random.PCG64(200 + n)), n, R)
+    print(f"shape edges n={n} R={R} h={h}", flush=True)
+    _compare(mdl.shape_descriptors(cp, k, h), shape.descriptors(cp, k, h), h, True)
+
+
+def test_long_thin_grid(mdl):
+    """Two points far apart along one axis on a coarse grid: the rows of the
+    grid do not fit the workspace beside the patches' results."""
+    cp, k = np.array([[0.0, 0.1, 0.2], [90.0, 0.3, -0.1], [45.0, -0.2, 0.4]])[:, [1, 2, 0]], np.array([6.0, 9.0, 7.0])
+    for order in ([0, 1, 2], [2, 0, 1], [1, 2, 0]):
+        g = mdl.shape_descriptors(cp[:, order], k, 2.3)
+        o = shape.descriptors(cp[:, order], k, 2.3)
+        _compare(g, o, 2.3, False)
+
+
+@pytest.mark.parametrize("scale", [1e-4, 1.0, 3e5])
+def test_no_unit_of_length(mdl, scale):
+    """The FP32 first decision works on coordinates scaled by the body's own
+    size: a body in other units has the same cells, area and columns."""
+    cp, k = workloads.random_body(np.random.Generator(np.random.PCG64(301)), 7, 5.0)
+    g = mdl.shape_descriptors(cp * scale, k * scale ** 2, 0.3 * scale)
+    o = shape.descriptors(cp * scale, k * scale ** 2, 0.3 * scale)
+    assert g["cells_inside"] == int(round(o["V"] / (0.3 * scale) ** 3))
+    assert g["S"] == pytest.approx(o["S"], rel=1e-12) and np.allclose(g["dims"], o["dims"], rtol=1e-10, atol=0)
+    assert abs(g["A_p"] - o["A_p"]) <= 2 * (0.3 * scale) ** 2
