@@ -55,6 +55,17 @@ class lbm_particle_state(C.Structure):
                 ("mass", C.c_double), ("volume", C.c_double), ("inertia", C.c_double * 9)]
 
 
+def _particle_dicts(arr, n):
+    # one copy of all records, of whose 30 numbers each body gets its own row's
+    # parts: a record at a time through ctypes took 1030 us for 200 bodies, this
+    # 186 us (one body: 7.4 and 7.1 us)
+    a = np.frombuffer(arr, np.float64, 30 * n).reshape(n, 30).copy()
+    return [{"x": x, "quat": quat, "v": v, "omega": omega, "F": F, "T": T, "m": m, "V": vol, "I": i}
+            for x, quat, v, omega, F, T, m, vol, i in zip(
+                a[:, 0:3], a[:, 3:7], a[:, 7:10], a[:, 10:13], a[:, 13:16], a[:, 16:19], a[:, 19].tolist(),
+                a[:, 20].tolist(), a[:, 21:30].reshape(n, 3, 3))]
+
+
 class mb_shape(C.Structure):
     _fields_ = [("V", C.c_double), ("S", C.c_double), ("A_p", C.c_double), ("dims", C.c_double * 3),
                 ("axes", C.c_double * 9), ("centroid", C.c_double * 3), ("d_n", C.c_double), ("d_s", C.c_double),
@@ -335,13 +346,7 @@ class Simulation:
     def particles(self):
         arr = (lbm_particle_state * max(self.np, 1))()
         _check(lib().lbm_get_particles(self._ctx, arr))
-        out = []
-        for j in range(self.np):
-            s = arr[j]
-            out.append({"x": np.array(s.x[:]), "quat": np.array(s.quat[:]), "v": np.array(s.v[:]),
-                        "omega": np.array(s.omega[:]), "F": np.array(s.F[:]), "T": np.array(s.T[:]),
-                        "m": s.mass, "V": s.volume, "I": np.array(s.inertia[:]).reshape(3, 3)})
-        return out
+        return _particle_dicts(arr, self.np)
 
     def set_particles(self, states):
         arr = (lbm_particle_state * max(self.np, 1))()

@@ -165,3 +165,19 @@ def test_mifit_sizes_and_argument_checks(mdl):
     assert L.mi_fitness(nul, 10, nul, 4, 4, nul, nul, 0, nul) == -1
     assert L.mi_ga(nul, 10, 4, 4, 1, 0.6, 0.5, 0.1, 0.1, nul, nul, nul, nul, nul, nul, 0, nul) == -1
     assert L.mi_gs(nul, nul, nul, nul, 1, 4, 1, 1e-3, nul, nul, nul) == -1
+
+
+@pytest.mark.parametrize("n", [0, 1, 3, 200])
+def test_particle_records_reach_python_unchanged(mdl, n):
+    arr = (mdl.lbm_particle_state * max(n, 1))()
+    np.frombuffer(arr, np.float64)[:] = np.random.default_rng(n).normal(size=30 * max(n, 1))
+    got = mdl._particle_dicts(arr, n)
+    assert len(got) == n
+    for s, p in zip(arr, got):
+        for key in ("x", "quat", "v", "omega", "F", "T"):
+            assert p[key].dtype == np.float64 and p[key].flags.c_contiguous and p[key].flags.writeable
+            assert p[key].tolist() == list(getattr(s, key))
+        assert p["I"].shape == (3, 3) and p["I"].ravel().tolist() == list(s.inertia)
+        assert type(p["m"]) is float and (p["m"], p["V"]) == (s.mass, s.volume)
+        p["x"][:] = 0.0  # the caller's own memory, not the record's
+        assert list(s.x) != [0.0, 0.0, 0.0]
