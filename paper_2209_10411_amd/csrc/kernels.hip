@@ -1863,6 +1863,19 @@ __device__ void special_update(const Params &p, const typename Store<S>::T *__re
     using T = typename Store<S>::T;
     float d[Q];
     uint32_t missing = 0u;
+    // the three coordinates an axis offers (wrapped; the node's own beyond a
+    // wall, where no direction pulls from) as parts of a node's index: with a
+    // branch per axis and direction the addresses took longer than the loads
+    // (48x48x80, one body: the classification 14.5 -> 11.9 us)
+    const auto axis = [](int c, int L, unsigned periodic, long long stride, long long o[3]) {
+        o[0] = stride * (c > 0 ? c - 1 : periodic ? L - 1 : c);
+        o[1] = stride * c;
+        o[2] = stride * (c < L - 1 ? c + 1 : periodic ? 0 : c);
+    };
+    long long cx[3], cy[3], cz[3];
+    axis(x, p.nx, p.periodic & 1u, 1, cx);
+    axis(y, p.ny, p.periodic & 2u, p.nx, cy);
+    axis(z, p.nz, p.periodic & 4u, (long long)p.nx * p.ny, cz);
     // every population's load is issued whatever its case, its address
     // chosen by selects (the resting wall's own opposite population, the
     // bounce-back value in B, the pulled value), so that all 19 are in
@@ -1871,8 +1884,7 @@ __device__ void special_update(const Params &p, const typename Store<S>::T *__re
     for (int i = 0; i < Q; ++i) {
         const bool w = (wall >> i) & 1u, sd = (solid >> i) & 1u;
         if (unc && (w || sd)) missing |= 1u << i;
-        long long src = n;  // kept beyond a wall
-        nbr(p, x, y, z, -EX[i], -EY[i], -EZ[i], src);
+        const long long src = cx[1 - EX[i]] + cy[1 - EY[i]] + cz[1 - EZ[i]];
         const T *base = sd && !w ? (const T *)B : A;
         const float v = Store<S>::ld(base, w ? pidx(n, OPP[i]) : pidx(sd ? n : src, i), p.inv_scale);
         d[i] = (unc && (w || sd)) ? 0.f : v;
@@ -1929,8 +1941,9 @@ __device__ void special_update(const Params &p, const typename Store<S>::T *__re
 // populations) and, in tiles along a surface, the instructions of the
 // boundary update: only a seventh of a wave's lanes hold such nodes there, so
 // the block first gathers them into one list (LDS) and one or two full waves
-// update them; the counts are ballots.  233 tiles: 17.5 -> 13.9 us; 46 673
-// tiles: 231 -> 218 us alone.
+// update them; the counts are ballots.  233 tiles: 17.5 -> 13.9 us (11.9 with
+// the branch-free addresses of special_update); 46 673 tiles: 231 -> 218 us
+// alone (204 with the tiles in eighths by XCD), 360 beside the stream-collide.
 template <int S>
 __device__ __forceinline__ void classify_body(const Params &p, const RegionMap &rm, const DevParticle *P,
                                               const int32_t *__restrict__ own_old,

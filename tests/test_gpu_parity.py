@@ -617,3 +617,25 @@ def test_fields_read_from_the_device(mdl, storage, size):
         assert np.array_equal(sim.particles()[0][k], twin.particles()[0][k])
     sim.close()
     twin.close()
+
+
+@pytest.mark.parametrize("periodic", range(8))
+def test_boundary_nodes_in_a_corner(mdl, periodic):
+    """A moving body across the periodic faces of a corner, just inside its
+    walls: boundary and uncovered nodes pull over every kind of face.  FP32
+    bounds of the fast cases (U ~ 0.07)."""
+    cfg = workloads.small_settling(n=24, nz=32, R=4.0)
+    cfg.nx, cfg.ny, cfg.nz = 20, 19, 23  # no multiple of a tile
+    cfg.periodic = periodic
+    p = cfg.particles[0]
+    p.cp_xyz, p.cp_k = np.zeros((1, 3)), np.array([16.0])  # a sphere: its surface reaches the nodes at the walls
+    p.x = np.array([0.7 if periodic >> a & 1 else p.bounding_radius() + 0.6 for a in range(3)])
+    p.v = np.array([0.06, 0.07, 0.05])
+    print(f"corner, periodic {periodic}", flush=True)
+    sim, ref = mdl.Simulation(cfg), oracle.Oracle(cfg)
+    for k in range(2):
+        sim.step(4)
+        ref.step(4)
+        compare_fields(sim, ref, drho_tol=DRHO_FAST, label=f"corner periodic={periodic} step {4 * (k + 1)}")
+    assert np.abs(sim.particles()[0]["x"] - ref.particle(0)["x"]).max() < 1e-6
+    sim.close()
