@@ -386,7 +386,8 @@ struct lbm_ctx {
     bool pending_refill;
     bool timing;
     int timing_every;  // time the stream-collide of every timing_every-th step
-    int bulk_blocks;  // stream-collide blocks per CU (0: the default cap), from the link count
+    int bulk_blocks;  // stream-collide blocks per CU (0: the default cap) with the bodies at rest
+    int bulk_blocks_coupled;  // and in a coupled step
     std::vector<hipEvent_t> ev;  // start/stop pairs
     size_t ev_used;
     long long timed_launches;
@@ -428,9 +429,31 @@ lbm_status check_device(lbm_ctx *c) {
     return LBM_OK;
 }
 
-// Flags from scratch for the current poses into the next buffer, node
-// classes against the current one, then the links of the new flags.  The
-// old flags stay in the dead buffer until refill() has used them.
+// Stream-collide blocks allowed per CU beside the boundary chain of a coupled
+// step.  The step is the longer of the two, and the fewer blocks, the faster the
+// chain (launches and memory round trips, some 55 us with one body, 85 with two
+// in contact) gets its waves in; the stream-collide itself loses little down to
+// four blocks (FP32) and a quarter at two.  So: the more nodes, the more blocks,
+// the lines drawn where the steps cross (us per step with six blocks -> with
+// those chosen; 16-bit: four -> chosen).
+//   FP32   two up to 1.6 M nodes    1.18 M nodes, one body: 71 -> 64; 0.82 M, two: 89 -> 83
+//          three up to 2.6 M        1.77 M: 79 -> 69 (two: 73); 2.18 M: 84 -> 75
+//          above, four              2.88 M: 92 -> 85 (three: 92); 2.76 M, two bodies: 117 -> 101;
+//                                   6.29 M: 163 -> 161; 6.55 M, two bodies: 179 -> 170
+//          five in lattice order above 5 M (rows no multiple of a wave)
+//                                   8.2 M: 210 -> 208 (four: 212); 16.4 M, two bodies: 421 -> 412 (417)
+//   16 bit two up to 2.9 M          1.77 M: 66 -> 64; 2.81 M: 74 -> 69; 2.76 M, two bodies: 98 -> 88
+//          above, four              4.19 M: 79 (two: 101, six: 90); 16.4 M, two bodies: 226 (254)
+//          five from 7.5 M nodes without contact  8.2 M: 120 -> 116; 16.8 M: 243 -> 239
+// Many cut links (more than one for 50 nodes) make the chain the longer one at
+// any size: two (256^3, 200 bodies, 1.45 M links: 1.52 against 1.64 ms with six).
+int bulk_blocks_beside_chain(const Params &p, long long n_links) {
+    const double m = (double)p.N / 1e6;
+    if (50 * n_links > (long long)p.N) return 2;
+    if (p.storage != 0) return m <= 2.9 ? 2 : m < 7.5 || p.contact ? 4 : 5;
+    return m <= 1.6 ? 2 : m <= 2.6 ? 3 : m > 5.0 && p.nx % 64 != 0 ? 5 : 4;
+}
+
 // Expected lengths of the link and boundary-node lists from the current ones
 // (bodies are rigid: their surface changes little), with a margin; the list
 // kernels stride over whatever the lists hold.  Synchronises.
@@ -439,16 +462,8 @@ lbm_status estimate_lists(lbm_ctx *c) {
     HIPCHK(hipStreamSynchronize(c->stream));
     HIPCHK(hipMemcpy(&h, c->cnt, sizeof h, hipMemcpyDeviceToHost));
     c->p.est_links = std::min(c->p.link_cap, (int)std::min<long long>(0x3fffffff, 3ll * h.n_links / 2 + 1024));
-    // Where the boundary chain outweighs the stream-collide (many cut links
-    // per node: on a 256^3 box with 200 bodies, 1.45 M links for 16.8 M
-    // nodes), the stream-collide leaves it more of every CU: two blocks per
-    // CU there gave 1.52 against 1.64 ms per step with six; with few links
-    // (7.5 k for 6.3 M nodes) six blocks keep the stream-collide at full speed.
-    // The 16-bit form (84 VGPRs, two nodes per lane) does best with four:
-    // its step is the boundary chain's, which runs faster with the room
-    // (settling 128x128x384: 0.118 -> 0.112 ms; two bodies 160x160x640:
-    // 0.262 -> 0.252 ms), while the kernel itself loses 2-3 %.
     c->bulk_blocks = 50ll * h.n_links > (long long)c->p.N ? 2 : c->p.storage != 0 ? 4 : 0;
+    c->bulk_blocks_coupled = c->p.np > 0 ? bulk_blocks_beside_chain(c->p, h.n_links) : c->bulk_blocks;
     // boundary nodes carry several cut links each (the special list is empty
     // right after set-up, when no previous flags exist)
     c->p.est_special = std::min(c->p.special_cap,
@@ -473,6 +488,9 @@ lbm_status body_counts(lbm_ctx *c, long long &solid, long long &refilled, long l
     return LBM_OK;
 }
 
+// Flags from scratch for the current poses into the next buffer, node
+// classes against the current one, then the links of the new flags.  The
+// old flags stay in the dead buffer until refill() has used them.
 lbm_status reflag(lbm_ctx *c) {
     launch_refresh_pose(c->p, c->P, 0, c->stream);
     launch_fill_i32(c->own[c->in], c->pl.N, FLUID, c->stream);
@@ -670,7 +688,7 @@ lbm_status lbm_init(const lbm_config *cfg, int32_t n_p, const lbm_particle *part
     c->ev_main = c->ev_flags = c->ev_links = c->ev_bulk = nullptr;
     c->timing = false;
     c->timing_every = 1;
-    c->bulk_blocks = 0;
+    c->bulk_blocks = c->bulk_blocks_coupled = 0;
     c->ev_used = 0;
     c->timed_launches = 0;
     c->timed_ms = 0;
@@ -840,6 +858,7 @@ lbm_status lbm_step(lbm_ctx *c, int32_t n_steps, int32_t mode) {
     for (int s = 0; s < n_steps; ++s) {
         StepArgs a = base_args(c);
         a.move = move;
+        if (move) a.bulk_blocks = c->bulk_blocks_coupled;
         if (!move) a.own_new = a.own_old;  // geometry fixed
         HIPCHK(hipStreamWaitEvent(c->aux, after, 0));
         StepArgs b = a;

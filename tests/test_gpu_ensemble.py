@@ -182,3 +182,29 @@ def test_one_lane_per_link_gives_the_same_bits(mdl):
         for a, b in zip(sim.links(), ref[3]):
             assert np.array_equal(a, b), f"case {i}: links differ"
     ens.close()
+
+
+@pytest.mark.parametrize("size,storage", [((64, 64, 96), workloads.STORE_F32), ((128, 128, 128), workloads.STORE_F32),
+                                          ((130, 130, 176), workloads.STORE_F32), ((130, 130, 300), workloads.STORE_F32),
+                                          ((65, 64, 97), workloads.STORE_BF16), ((201, 200, 190), workloads.STORE_F16)])
+def test_room_left_to_the_boundary_chain_changes_no_bit(mdl, size, storage):
+    """Alone, the stream-collide's blocks per CU go by the number of nodes (two
+    to five at these sizes); in a batch they do not.  Same fields and bodies
+    (16-bit rows of odd length: pairs of nodes, which a batch does not form,
+    round differently)."""
+    cfg = workloads.small_settling(n=24, nz=40, R=6.0, g=5e-4)
+    cfg.nx, cfg.ny, cfg.nz = size
+    cfg.particles[0].x = np.array([s / 2 for s in size])
+    cfg.storage = storage
+    print(f"room for the chain, {size}, storage {storage}", flush=True)
+    sim, ens = mdl.Simulation(cfg), mdl.Ensemble([cfg])
+    sim.step(12)
+    ens.step(12)
+    own = sim.owner()
+    assert np.array_equal(own, ens.cases[0].owner())
+    for a, b in zip(sim.macros(), ens.cases[0].macros()):
+        assert np.array_equal(a[own < 0], b[own < 0])
+    for key in ("x", "quat", "v", "omega", "F", "T"):
+        assert np.array_equal(sim.particles()[0][key], ens.cases[0].particles()[0][key])
+    ens.close()
+    sim.close()
