@@ -2694,7 +2694,8 @@ long long link_q_expected(const Params &p) { return p.np > 0 ? expected_links(p)
 constexpr int LINK_GUESS_BLOCKS = 1024;  // 4096 waves, each loads the network once
 
 // LDS reserved (and not used) by each stream-collide block, so that at most
-// BULK_MAX_WAVES_PER_SIMD of its waves share a SIMD.  Its FP32 form needs 52
+// max_blocks of them share a CU (bulk_blocks_beside_chain in api.cpp says how
+// many in a coupled step), else BULK_MAX_WAVES_PER_SIMD of their waves a SIMD.  Its FP32 form needs 52
 // VGPRs, so without a cap it fills all eight wave slots of every SIMD and the
 // boundary kernels on the second stream (up to 128 VGPRs a wave) find no room
 // until the stream-collide drains: the step becomes their sum instead of their
@@ -2839,7 +2840,11 @@ template <int S>
 static void launch_bulk_batch_t(int bw, const BulkCase *cases, const int *blk_case, int nblocks, int parity,
                                 hipStream_t s) {
     if (nblocks <= 0) return;
-    if (bw == 4) k_bulk_batch<S, 4><<<nblocks, 256, bulk_lds_reserve(4), s>>>(cases, blk_case, parity);
+    // Seven blocks of four waves per CU: an ensemble's stream-collide is much longer
+    // than the boundary kernels beside it, which want less room (24 systems, us
+    // per step with six, seven and eight: FP32 985, 970, 1001, BF16 824, 764, 782;
+    // 64 systems, FP32: 2460, 2431, 2365)
+    if (bw == 4) k_bulk_batch<S, 4><<<nblocks, 256, bulk_lds_reserve(4, 7), s>>>(cases, blk_case, parity);
     else k_bulk_batch<S, 8><<<nblocks, 512, bulk_lds_reserve(8), s>>>(cases, blk_case, parity);
 }
 
