@@ -43,7 +43,7 @@ size_t mi_fitness_work_bytes(int64_t m, int32_t P);
 /* GA evaluation (sec. 2.2, Evaluation): F[p] = sum_i (f(H_i; pop_p) - 1)^2
  * for each of the P individuals pop [P][n][4] over the hull H [m][3]; F [P]
  * FP64.  A block takes one individual and a chunk of up to 2048 hull points
- * (control points in LDS, one hull point per lane, fixed-order block sums);
+ * (control points in LDS, hull points over the lanes, fixed-order block sums);
  * with several chunks the per-chunk sums go to the workspace (work,
  * work_bytes >= mi_fitness_work_bytes) and a second launch adds them in chunk
  * order.  Asynchronous. */
