@@ -355,3 +355,33 @@ def test_gradient_of_ragged_batches(mdl, n):
     gr = omlp.grad(th, Xr.astype(np.float64), Tr.astype(np.float64))
     assert np.abs(g - gr).max() <= 1e-5 * np.abs(gr).max()
     assert loss == pytest.approx(omlp.loss(th, Xr.astype(np.float64), Tr.astype(np.float64)), rel=1e-5)
+
+
+@pytest.mark.parametrize("n,layer", [(5, "W1"), (40, "W1"), (5, "W2"), (300, "W2")])
+def test_gradient_with_a_weight_beyond_fp16(mdl, n, layer):
+    """A weight that FP16 holds as infinite saturates its unit (or, in the
+    second layer, the unit it feeds) for every sample; the gradients of the
+    layers above it stay finite, also where a slice ends within a tile.  (The
+    FP16 form's bound of the test above; the oracle takes a large finite
+    weight, which saturates tanh as well.)"""
+    import torch
+    rng = np.random.default_rng(400 + n)
+    X, T = rand_batch(rng, n)
+    X[:, 0] = np.where(np.abs(X[:, 0]) < 0.1, 0.3, X[:, 0])
+    theta = params(15).astype(np.float32)
+    big = 0 * 64 + 3 if layer == "W1" else 87 * 64 + 64 + 5 * 64 + 3
+    theta[big] = 1e6
+    th = theta.astype(np.float16).astype(np.float64)
+    th[big] = 6e4
+    Xr, Tr = X.astype(np.float16), T.astype(np.float32)
+    g, loss = mdl.Mlp(theta).grad(torch.tensor(Xr, device="cuda:0"), torch.tensor(Tr, device="cuda:0"), 0)
+    gr = omlp.grad(th, Xr.astype(np.float64), Tr.astype(np.float64))
+    # what the infinite weight itself carries back (second layer: to unit 5 of
+    # the first) is 0 times infinity; the rest is held to the bound
+    ok = np.ones(omlp.P, bool)
+    if layer == "W2":
+        ok[np.arange(87) * 64 + 5] = False
+        ok[87 * 64 + 5] = False
+    assert np.all(np.isfinite(g[ok]))
+    assert np.abs(g[ok] - gr[ok]).max() <= 2e-2 * np.abs(gr[ok]).max()
+    assert loss == pytest.approx(omlp.loss(th, Xr.astype(np.float64), Tr.astype(np.float64)), rel=2e-2)
