@@ -564,14 +564,17 @@ lbm_status mi_gs(const double *hulls, const int64_t *hull_off, const double *pla
     delete[] ho;
     if (!ok) return LBM_E_INVALID;
     const bool staged = most <= GS_STAGED;
-    auto run = [&](auto kernel, size_t lds) {
-        // (beyond 64 KB of LDS a kernel asks for it; the largest here is 130 KB)
-        if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    // Beyond 64 KB of LDS a kernel asks for it, and the request belongs to the
+    // kernel, not to the launch: it is each form's largest (130 and 82 KB with
+    // the static 34) in every call, so that calls on several threads agree.
+    auto run = [&](auto kernel, int max_lds, size_t lds) {
+        if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds) != hipSuccess)
             return LBM_E_HIP;
         kernel<<<B, GS_BLK, lds, s>>>(hulls, hull_off, planes, plane_off, n, E, eta, M, loss);
         return launched();
     };
-    return staged ? run(k_gs<true>, 32 * (size_t)most) : run(k_gs<false>, 8 * (size_t)most);
+    return staged ? run(k_gs<true>, 32 * GS_STAGED, 32 * (size_t)most)
+                  : run(k_gs<false>, 8 * MI_GS_MAXPTS, 8 * (size_t)most);
 }
 
 // ---------------------------------------------- fitness without allocation
