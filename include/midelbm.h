@@ -180,7 +180,9 @@ lbm_status particle_forces(lbm_ctx *ctx, double *F, double *T);
 lbm_status refill(lbm_ctx *ctx, int64_t *n_refilled);
 
 /* ---- state access for tests and I/O (host FP64 arrays; all synchronise) ---- */
-/* rho [N] and u [N][3] of the stored state (u excludes the half body force). */
+/* rho [N] and u [N][3] of the stored state (u excludes the half body force).
+ * The fields pass through the arena's next flag buffer, which holds no state
+ * between steps and is cleared again before the call returns. */
 lbm_status lbm_get_macros(lbm_ctx *ctx, double *rho, double *u);
 /* Full post-collision populations f_i = w_i rho0 + deviation, [19][N]. */
 lbm_status lbm_get_populations(lbm_ctx *ctx, double *f);

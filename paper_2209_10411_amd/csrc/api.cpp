@@ -1006,6 +1006,7 @@ lbm_status lbm_get_macros(lbm_ctx *c, double *rho, double *u) {
     launch_fill_i32(c->own[c->in], N, FLUID, c->stream);
     HIPCHK(e);
     HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(c->stream));  // the buffer is whole again when the call returns
     return LBM_OK;
 }
 

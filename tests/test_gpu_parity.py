@@ -639,3 +639,21 @@ def test_boundary_nodes_in_a_corner(mdl, periodic):
         compare_fields(sim, ref, drho_tol=DRHO_FAST, label=f"corner periodic={periodic} step {4 * (k + 1)}")
     assert np.abs(sim.particles()[0]["x"] - ref.particle(0)["x"]).max() < 1e-6
     sim.close()
+
+
+def test_read_out_leaves_nothing_on_the_stream(mdl):
+    """The field read-out synchronises: what it does to the arena is done when
+    it returns (a box large enough that clearing its scratch takes longer than
+    the return)."""
+    import torch
+    cfg = workloads.Config(nx=256, ny=256, nz=256, periodic=7, tau=0.7)
+    sim = mdl.Simulation(cfg)
+    sim.step(2)
+    rho, u = np.zeros(cfg.n_nodes), np.zeros(3 * cfg.n_nodes)
+    L, dp = mdl.lib(), mdl._dptr
+    idle = []
+    for _ in range(5):
+        assert L.lbm_get_macros(sim._ctx, dp(rho), dp(u)) == 0
+        idle.append(torch.cuda.current_stream().query())
+    assert all(idle), idle
+    sim.close()
