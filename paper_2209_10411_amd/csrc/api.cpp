@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -384,6 +385,7 @@ struct lbm_ctx {
     hipStream_t aux;              // second stream: link build overlapped with stream-collide
     hipEvent_t ev_main, ev_flags, ev_links, ev_bulk;
     bool pending_refill;
+    std::mutex scratch;  // held while the next flag buffer carries read-out fields
     bool timing;
     int timing_every;  // time the stream-collide of every timing_every-th step
     int bulk_blocks;  // stream-collide blocks per CU (0: the default cap) with the bodies at rest
@@ -993,6 +995,9 @@ lbm_status lbm_get_macros(lbm_ctx *c, double *rho, double *u) {
     // The fields pass through the next flag buffer (4 bytes a node, 32 a node
     // needed: nine turns at most), which is all FLUID between steps and is made
     // so again: no other memory of the arena is free for them.
+    // One read-out at a time, and none while the buffer is being saved: calls
+    // that only read the state may come from several threads.
+    std::lock_guard<std::mutex> hold(c->scratch);
     const long long N = c->pl.N, chunk = std::max<long long>(1, 4 * N / 32);
     double *drho = (double *)c->own[c->in];
     hipError_t e = hipSuccess;
@@ -1386,6 +1391,7 @@ lbm_status lbm_save(lbm_ctx *c, const char *path) {
     h.p = c->p;
     FILE *f = fopen(path, "wb");
     if (!f) return fail(LBM_E_INVALID, "cannot open %s for writing", path);
+    std::lock_guard<std::mutex> hold(c->scratch);
     bool ok = fwrite(&h, sizeof h, 1, f) == 1 && fwrite(sig.data(), 8, sig.size(), f) == sig.size();
     std::vector<char> buf(std::min(CKPT_CHUNK, c->pl.total));
     for (size_t o = 0; ok && o < c->pl.total; o += buf.size()) {

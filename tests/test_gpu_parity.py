@@ -657,3 +657,44 @@ def test_read_out_leaves_nothing_on_the_stream(mdl):
         idle.append(torch.cuda.current_stream().query())
     assert all(idle), idle
     sim.close()
+
+
+def test_read_outs_from_several_threads(mdl, tmp_path):
+    """Reading the fields and saving the state change nothing and may come from
+    several threads at once: every read-out and every file is the one of the
+    calls made alone, and the steps that follow are those of a system that was
+    not read."""
+    import threading
+    cfg = workloads.small_settling()
+    sim, quiet = mdl.Simulation(cfg), mdl.Simulation(cfg)
+    sim.step(5)
+    quiet.step(5)
+    ref = sim.macros()
+    sim.save(str(tmp_path / "alone"))
+    alone = (tmp_path / "alone").read_bytes()
+    bad = []
+
+    def read():
+        for _ in range(15):
+            r = sim.macros()
+            if not (np.array_equal(r[0], ref[0]) and np.array_equal(r[1], ref[1])):
+                bad.append("fields")
+
+    def save():
+        for k in range(4):
+            sim.save(str(tmp_path / "beside"))
+            if (tmp_path / "beside").read_bytes() != alone:
+                bad.append("file")
+
+    threads = [threading.Thread(target=f) for f in (read, read, save)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
+    sim.step(5)
+    quiet.step(5)
+    assert np.array_equal(sim.populations(), quiet.populations())
+    assert np.array_equal(sim.owner(), quiet.owner())
+    sim.close()
+    quiet.close()
