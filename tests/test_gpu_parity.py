@@ -698,3 +698,26 @@ def test_read_outs_from_several_threads(mdl, tmp_path):
     assert np.array_equal(sim.owner(), quiet.owner())
     sim.close()
     quiet.close()
+
+
+@pytest.mark.parametrize("storage,size", [(workloads.STORE_F32, (3, 3, 3)), (workloads.STORE_F32, (22, 22, 24)),
+                                          (workloads.STORE_F32, (20, 24, 25)), (workloads.STORE_F16, (13, 13, 15)),
+                                          (workloads.STORE_F16, (12, 15, 15)), (workloads.STORE_BF16, (11, 29, 37))])
+def test_fields_of_small_lattices(mdl, storage, size):
+    """The read-out on the host (below 12 000 nodes, 2700 in FP16) and the one
+    on the device, around the lines between them: the moments of the
+    populations, 40 roundings of the largest term's sum."""
+    cfg = workloads.Config(nx=size[0], ny=size[1], nz=size[2], periodic=7, tau=0.7, storage=storage,
+                           g_fluid=np.array([1e-6, 0.0, 2e-6]))
+    sim = mdl.Simulation(cfg)
+    sim.set_populations(oracle.lattice()[1][:, None] + workloads.random_populations(55, cfg.n_nodes), post_collision=True)
+    sim.step(2)
+    f = sim.populations()
+    rho, u = sim.macros()
+    r = f.sum(0)
+    bound = 40 * 2.0 ** -53 * np.abs(f).sum(0)
+    assert np.all(np.abs(rho - r) <= bound)
+    for a, E in enumerate(oracle.lattice()[0].T):
+        v = (E[:, None] * f).sum(0) / r - 0.5 * cfg.g_fluid[a]
+        assert np.all(np.abs(u[:, a] - v) <= 2 * bound / r + 2.0 ** -52 * np.abs(v))
+    sim.close()
