@@ -104,8 +104,43 @@ __device__ __forceinline__ void centre(const Grid &G, long long t, double c[3], 
     for (int a = 0; a < 3; ++a) c[a] = G.lo[a] + G.h * ((double)idx[a] + 0.5);
 }
 
+// Inside decision at a point: coordinates about the anchor (the mean control
+// point) scaled so that sqrt(sum k) is 16, in FP32; terms k * rcp(|d|^2) on the
+// hardware reciprocal (1 ulp).  With every |d|^2 >= 1 each component of d is off
+// by at most u (|r_a| + |p_a| + |d_a|) (u = 2^-24), so |d|^2 by at most
+// u (2.03 (|r|_1 + |p|_1) + 6.5) relative, a term by that plus 3 u, and the
+// n-term sum by n u more; with a factor 1.5 (the scaling's own roundings are
+// below it) and 1e-12 for the exact sum's.  Within the bound of 1, or within
+// 1 of a control point, the exact quotients decide (cm1).
+struct Body32 {
+    float4 f[MAXN];  // scaled position about the anchor, scaled weight
+    double anc[3], scale;
+    float bp;  // max |p - anchor|_1
+};
+
+__device__ __forceinline__ bool inside(const Body &b, const Body32 &q, double x, double y, double z) {
+    const float rx = (float)((x - q.anc[0]) * q.scale), ry = (float)((y - q.anc[1]) * q.scale),
+                rz = (float)((z - q.anc[2]) * q.scale);
+    float C = 0.f, rmin = 1.f;
+    for (int j = 0; j < b.n; ++j) {
+        const float4 c = q.f[j];
+        const float dx = rx - c.x, dy = ry - c.y, dz = rz - c.z;
+        const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+        rmin = fminf(rmin, d2);
+        C = fmaf(c.w, __builtin_amdgcn_rcpf(d2), C);
+    }
+    if (rmin >= 1.f) {
+        const float ax = fabsf(rx) + fabsf(ry) + fabsf(rz);
+        const double rel = 1.5 * 5.9604644775390625e-8 * (2.03 * ((double)ax + (double)q.bp) + 9.5 + b.n);
+        if ((double)C * (1.0 - rel) > 1.0 + 1e-12) return true;
+        if ((double)C * (1.0 + rel) < 1.0 - 1e-12) return false;
+    }
+    return cm1(b, x, y, z) >= 0.0;
+}
+
 // ---------------------------------------------------------- general form
-// Every cell by itself (passes 1 to 3); mb_shape_descriptors says when.
+// Every cell by itself (passes 1 to 3); mb_shape_descriptors says when.  All
+// but the area needs the inside decisions alone (inside).
 // Pass 1: inside count, first moments of the inside centres, surface area.
 __global__ __launch_bounds__(BLK) void k_shape_grid(Body b, Grid G, long long cells, double *__restrict__ part) {
 #pragma clang fp contract(off)
@@ -148,8 +183,27 @@ __global__ __launch_bounds__(BLK) void k_shape_grid(Body b, Grid G, long long ce
     }
 }
 
+// First moments alone: the sums of pass 1, in its order.
+__global__ __launch_bounds__(BLK) void k_shape_centre(Body b, Body32 q, Grid G, long long cells,
+                                                      double *__restrict__ part) {
+    __shared__ double red[4];
+    const long long t = blockIdx.x * (long long)BLK + threadIdx.x;
+    double v[3] = {0.0, 0.0, 0.0};
+    if (t < cells) {
+        double c[3];
+        int idx[3];
+        centre(G, t, c, idx);
+        if (inside(b, q, c[0], c[1], c[2]))
+            for (int a = 0; a < 3; ++a) v[a] = c[a];
+    }
+    for (int a = 0; a < 3; ++a) {
+        const double s = block_sum(v[a], red);
+        if (threadIdx.x == 0) part[3 * blockIdx.x + a] = s;
+    }
+}
+
 // Pass 2: second moments about the centroid c of the inside centres.
-__global__ __launch_bounds__(BLK) void k_shape_moments(Body b, Grid G, long long cells, double cx, double cy,
+__global__ __launch_bounds__(BLK) void k_shape_moments(Body b, Body32 q, Grid G, long long cells, double cx, double cy,
                                                        double cz, double *__restrict__ part) {
 #pragma clang fp contract(off)
     __shared__ double red[4];
@@ -159,22 +213,22 @@ __global__ __launch_bounds__(BLK) void k_shape_moments(Body b, Grid G, long long
         double c[3];
         int idx[3];
         centre(G, t, c, idx);
-        if (cm1(b, c[0], c[1], c[2]) >= 0.0) {
+        if (inside(b, q, c[0], c[1], c[2])) {
             const double r[3] = {c[0] - cx, c[1] - cy, c[2] - cz};
             m[0] = r[0] * r[0]; m[1] = r[1] * r[1]; m[2] = r[2] * r[2];
             m[3] = r[0] * r[1]; m[4] = r[0] * r[2]; m[5] = r[1] * r[2];
         }
     }
-    for (int q = 0; q < 6; ++q) {
-        const double s = block_sum(m[q], red);
-        if (threadIdx.x == 0) part[6 * blockIdx.x + q] = s;
+    for (int e = 0; e < 6; ++e) {
+        const double s = block_sum(m[e], red);
+        if (threadIdx.x == 0) part[6 * blockIdx.x + e] = s;
     }
 }
 
 // Pass 3: min and max of the inside centres projected on the three axes
 // (rows of ax), relative to the centroid.
-__global__ __launch_bounds__(BLK) void k_shape_extent(Body b, Grid G, long long cells, double cx, double cy, double cz,
-                                                      Axes A, double *__restrict__ part) {
+__global__ __launch_bounds__(BLK) void k_shape_extent(Body b, Body32 q, Grid G, long long cells, double cx,
+                                                      double cy, double cz, Axes A, double *__restrict__ part) {
 #pragma clang fp contract(off)
     __shared__ double red[4];
     const double *ax = A.a;
@@ -184,7 +238,7 @@ __global__ __launch_bounds__(BLK) void k_shape_extent(Body b, Grid G, long long 
         double c[3];
         int idx[3];
         centre(G, t, c, idx);
-        if (cm1(b, c[0], c[1], c[2]) >= 0.0) {
+        if (inside(b, q, c[0], c[1], c[2])) {
             const double r[3] = {c[0] - cx, c[1] - cy, c[2] - cz};
             for (int a = 0; a < 3; ++a) {
                 const double pr = (r[0] * ax[3 * a] + r[1] * ax[3 * a + 1]) + r[2] * ax[3 * a + 2];
@@ -203,42 +257,9 @@ __global__ __launch_bounds__(BLK) void k_shape_extent(Body b, Grid G, long long 
 }
 
 // ------------------------------------------------------------- slab form
-// The same decisions, with each grid sample evaluated once, first in FP32.
+// The same decisions, with each grid sample evaluated once, first in FP32
+// (inside).
 //
-// Inside decision at a point: coordinates about the anchor (the mean control
-// point) scaled so that sqrt(sum k) is 16, in FP32; terms k * rcp(|d|^2) on the
-// hardware reciprocal (1 ulp).  With every |d|^2 >= 1 each component of d is off
-// by at most u (|r_a| + |p_a| + |d_a|) (u = 2^-24), so |d|^2 by at most
-// u (2.03 (|r|_1 + |p|_1) + 6.5) relative, a term by that plus 3 u, and the
-// n-term sum by n u more; with a factor 1.5 (the scaling's own roundings are
-// below it) and 1e-12 for the exact sum's.  Within the bound of 1, or within
-// 1 of a control point, the exact quotients decide (cm1).
-struct Body32 {
-    float4 f[MAXN];  // scaled position about the anchor, scaled weight
-    double anc[3], scale;
-    float bp;  // max |p - anchor|_1
-};
-
-__device__ __forceinline__ bool inside(const Body &b, const Body32 &q, double x, double y, double z) {
-    const float rx = (float)((x - q.anc[0]) * q.scale), ry = (float)((y - q.anc[1]) * q.scale),
-                rz = (float)((z - q.anc[2]) * q.scale);
-    float C = 0.f, rmin = 1.f;
-    for (int j = 0; j < b.n; ++j) {
-        const float4 c = q.f[j];
-        const float dx = rx - c.x, dy = ry - c.y, dz = rz - c.z;
-        const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-        rmin = fminf(rmin, d2);
-        C = fmaf(c.w, __builtin_amdgcn_rcpf(d2), C);
-    }
-    if (rmin >= 1.f) {
-        const float ax = fabsf(rx) + fabsf(ry) + fabsf(rz);
-        const double rel = 1.5 * 5.9604644775390625e-8 * (2.03 * ((double)ax + (double)q.bp) + 9.5 + b.n);
-        if ((double)C * (1.0 - rel) > 1.0 + 1e-12) return true;
-        if ((double)C * (1.0 + rel) < 1.0 - 1e-12) return false;
-    }
-    return cm1(b, x, y, z) >= 0.0;
-}
-
 // Node and centre coordinates along axis a, as written in pass 1.
 __device__ __forceinline__ double node_at(const Grid &G, int a, int i) {
 #pragma clang fp contract(off)
@@ -624,9 +645,18 @@ lbm_status mb_shape_descriptors(const double *cp, const double *k, int32_t n, do
         q.bp = std::fmax(q.bp, l1 * (1.f + 1e-6f));
     }
     // The slab form needs its rows and block results in the workspace (they do
-    // not fit a short grid of long rows).  One control point keeps the general
-    // form: the sphere's moments are equal but for their roundings, which alone
-    // choose its axes, and the general form's sums are the ones it always had.
+    // not fit a short grid of long rows).
+    //
+    // Where two principal moments are equal but for roundings (a sphere, a
+    // dumbbell or a cube that lies with the grid), the roundings of their sums
+    // alone choose the axes, and with them dims and A_p: such a body takes its
+    // centroid and moments from the general form's sums, the ones it always
+    // had, and so do the extents, whose rows share the workspace with them.
+    // (Equal: within 1e-4 of the largest; a gap of that leaves the axes, of
+    // moments exact to 1e-14, good to 1e-10.)  With the three more passes and
+    // read-backs two coincident points, radius 8, take 193 us at cell 0.25 and
+    // 488 at 0.1; every pass in the general form, 240 and 920.  One control
+    // point, a sphere, does without the slab form.
     const int segs = (int)cdiv(G.n[0], SEG), py = (int)cdiv(G.n[1], SLAB), pz = (int)cdiv(G.n[2], SLAB);
     const long long slabs = (long long)segs * py * pz, n_rows = (long long)segs * G.n[1] * G.n[2];
     const size_t slab_bytes = sizeof(SlabOut) * (size_t)slabs;
@@ -635,7 +665,16 @@ lbm_status mb_shape_descriptors(const double *cp, const double *k, int32_t n, do
     const size_t row_end = (slab_bytes + 2 * (size_t)n_rows + 7) / 8;  // in doubles; the extents' slots follow
     const long long room = 6 * blocks - (long long)row_end, ext_blocks = std::min<long long>(256, room / 6);
     const bool slab_form = n > 1 && ext_blocks >= 1 && slabs < (1ll << 31);
+    bool rows_kept = slab_form;
     double cnt = 0, area = 0, c[3], m[6] = {0, 0, 0, 0, 0, 0};
+    auto sum_moments = [&]() {  // pass 2
+        k_shape_moments<<<(unsigned)blocks, BLK, 0, s>>>(b, q, G, cells, c[0], c[1], c[2], part);
+        if (hipGetLastError() != hipSuccess || !fetch(6 * blocks)) return false;
+        for (int a = 0; a < 6; ++a) m[a] = 0.0;
+        for (long long e = 0; e < blocks; ++e)
+            for (int a = 0; a < 6; ++a) m[a] += hp[6 * e + a];
+        return true;
+    };
     if (slab_form) {
         k_shape_slab<<<(unsigned)slabs, BLK, 0, s>>>(b, q, G, py, pz, slab, rows);
         std::vector<SlabOut> so((size_t)slabs);
@@ -666,6 +705,20 @@ lbm_status mb_shape_descriptors(const double *cp, const double *k, int32_t n, do
         const int pa[6] = {0, 1, 2, 0, 0, 1}, pb[6] = {0, 1, 2, 1, 2, 2};
         for (int e2 = 0; e2 < 6; ++e2)
             m[e2] = h * h * (double)(((long double)(N * T[e2] - S[pa[e2]] * S[pb[e2]])) / (long double)N);
+        double D[3][3] = {{m[0], m[3], m[4]}, {m[3], m[1], m[5]}, {m[4], m[5], m[2]}}, W[3][3];
+        jacobi3(D, W);
+        double w[3] = {D[0][0], D[1][1], D[2][2]};
+        std::sort(w, w + 3);
+        if (std::min(w[1] - w[0], w[2] - w[1]) <= 1e-4 * w[2]) {
+            rows_kept = false;
+            k_shape_centre<<<(unsigned)blocks, BLK, 0, s>>>(b, q, G, cells, part);
+            if (hipGetLastError() != hipSuccess || !fetch(3 * blocks)) return LBM_E_HIP;
+            double sum[3] = {0, 0, 0};
+            for (long long e = 0; e < blocks; ++e)
+                for (int a = 0; a < 3; ++a) sum[a] += hp[3 * e + a];
+            for (int a = 0; a < 3; ++a) c[a] = sum[a] / cnt;
+            if (!sum_moments()) return LBM_E_HIP;
+        }
     } else {
         // pass 1
         k_shape_grid<<<(unsigned)blocks, BLK, 0, s>>>(b, G, cells, part);
@@ -676,11 +729,7 @@ lbm_status mb_shape_descriptors(const double *cp, const double *k, int32_t n, do
         }
         if (!(cnt > 0.0)) return LBM_E_INVALID;
         c[0] = sx / cnt; c[1] = sy / cnt; c[2] = sz / cnt;
-        // pass 2
-        k_shape_moments<<<(unsigned)blocks, BLK, 0, s>>>(b, G, cells, c[0], c[1], c[2], part);
-        if (hipGetLastError() != hipSuccess || !fetch(6 * blocks)) return LBM_E_HIP;
-        for (long long e = 0; e < blocks; ++e)
-            for (int a = 0; a < 6; ++a) m[a] += hp[6 * e + a];
+        if (!sum_moments()) return LBM_E_HIP;
     }
     double A[3][3] = {{m[0], m[3], m[4]}, {m[3], m[1], m[5]}, {m[4], m[5], m[2]}}, V[3][3];
     jacobi3(A, V);
@@ -695,12 +744,12 @@ lbm_status mb_shape_descriptors(const double *cp, const double *k, int32_t n, do
     // pass 3
     Axes A3, A4;
     memcpy(A3.a, ax, sizeof ax);
-    const long long eb = slab_form ? std::min(ext_blocks, cdiv(n_rows, BLK)) : blocks;
-    if (slab_form)
+    const long long eb = rows_kept ? std::min(ext_blocks, cdiv(n_rows, BLK)) : blocks;
+    if (rows_kept)
         k_shape_rows<<<(unsigned)eb, BLK, 0, s>>>(G, segs, c[0], c[1], c[2], A3, rows, part + row_end);
     else
-        k_shape_extent<<<(unsigned)blocks, BLK, 0, s>>>(b, G, cells, c[0], c[1], c[2], A3, part);
-    if (hipGetLastError() != hipSuccess || !fetch(6 * eb, slab_form ? row_end : 0)) return LBM_E_HIP;
+        k_shape_extent<<<(unsigned)blocks, BLK, 0, s>>>(b, q, G, cells, c[0], c[1], c[2], A3, part);
+    if (hipGetLastError() != hipSuccess || !fetch(6 * eb, rows_kept ? row_end : 0)) return LBM_E_HIP;
     double mn[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL}, mx[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL};
     for (long long e = 0; e < eb; ++e)
         for (int a = 0; a < 3; ++a) {

@@ -129,3 +129,18 @@ def test_no_unit_of_length(mdl, scale):
     assert g["cells_inside"] == int(round(o["V"] / (0.3 * scale) ** 3))
     assert g["S"] == pytest.approx(o["S"], rel=1e-12) and np.allclose(g["dims"], o["dims"], rtol=1e-10, atol=0)
     assert abs(g["A_p"] - o["A_p"]) <= 2 * (0.3 * scale) ** 2
+
+
+@pytest.mark.parametrize("h", [0.31, 0.25])
+@pytest.mark.parametrize("n", [2, 4])
+def test_sphere_of_coincident_points(mdl, n, h):
+    """n points of weight K / n in one place are the point of weight K (n a
+    power of two: C is the same to the bit).  The roundings of a sphere's
+    moments choose its axes: both bodies' must be summed alike."""
+    for p in ([0.0, 0.0, 0.0], [0.1, 0.2, 0.3]):
+        one = mdl.shape_descriptors(np.array([p]), np.array([64.0]), h)
+        more = mdl.shape_descriptors(np.array([p] * n), np.full(n, 64.0 / n), h)
+        assert more["cells_inside"] == one["cells_inside"] and more["columns_hit"] == one["columns_hit"]
+        assert np.array_equal(more["dims"], one["dims"]) and np.array_equal(more["axes"], one["axes"])
+        assert np.array_equal(more["centroid"], one["centroid"])
+        assert more["S"] == pytest.approx(one["S"], rel=1e-12)
