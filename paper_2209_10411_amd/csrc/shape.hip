@@ -110,8 +110,10 @@ __device__ __forceinline__ void centre(const Grid &G, long long t, double c[3], 
 // by at most u (|r_a| + |p_a| + |d_a|) (u = 2^-24), so |d|^2 by at most
 // u (2.03 (|r|_1 + |p|_1) + 6.5) relative, a term by that plus 3 u, and the
 // n-term sum by n u more; with a factor 1.5 (the scaling's own roundings are
-// below it) and 1e-12 for the exact sum's.  Within the bound of 1, or within
-// 1 of a control point, the exact quotients decide (cm1).
+// below it) and 1e-12 for the exact sum's.  Within the bound of 1, within
+// 1 of a control point, or where the bound exceeds 1/4 (a body 1e5 times as long
+// as its radius: the errors' squares, left out of it, then count), the exact
+// quotients decide (cm1).
 struct Body32 {
     float4 f[MAXN];  // scaled position about the anchor, scaled weight
     double anc[3], scale;
@@ -132,8 +134,8 @@ __device__ __forceinline__ bool inside(const Body &b, const Body32 &q, double x,
     if (rmin >= 1.f) {
         const float ax = fabsf(rx) + fabsf(ry) + fabsf(rz);
         const double rel = 1.5 * 5.9604644775390625e-8 * (2.03 * ((double)ax + (double)q.bp) + 9.5 + b.n);
-        if ((double)C * (1.0 - rel) > 1.0 + 1e-12) return true;
-        if ((double)C * (1.0 + rel) < 1.0 - 1e-12) return false;
+        if (rel < 0.25 && (double)C * (1.0 - rel) > 1.0 + 1e-12) return true;
+        if (rel < 0.25 && (double)C * (1.0 + rel) < 1.0 - 1e-12) return false;
     }
     return cm1(b, x, y, z) >= 0.0;
 }

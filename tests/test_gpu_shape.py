@@ -144,3 +144,25 @@ def test_sphere_of_coincident_points(mdl, n, h):
         assert np.array_equal(more["dims"], one["dims"]) and np.array_equal(more["axes"], one["axes"])
         assert np.array_equal(more["centroid"], one["centroid"])
         assert more["S"] == pytest.approx(one["S"], rel=1e-12)
+
+
+def test_light_point_far_from_the_rest(mdl):
+    """A body so long (2e7 for a radius of 16) that FP32 no longer separates a
+    cell's centre from the light control point 0.24 away: the centre lies
+    inside.  The cells are counted in FP64 about each control point."""
+    h, k = 16.0, np.array([255.6, 0.1, 0.2])
+    r = np.sqrt(k.sum())
+    lo = np.full(3, -r - h)
+    cp = np.array([[0.0, 0.0, 0.0], [0.0, 0.0, 0.0], [3.0, 260.0, 251.0]])
+    cp[1] = lo + h * (np.array([1249978, 2, 2]) + 0.5) + [-0.186, -0.143, 0.052]
+    cells = set()
+    for p in cp:
+        mid = np.floor((p - lo) / h).astype(int)
+        for d in np.ndindex(7, 7, 7):
+            i = mid + np.array(d) - 3
+            c = lo + h * (i + 0.5)
+            if np.all(i >= 0) and (k / ((c - cp) ** 2).sum(1)).sum() >= 1.0:
+                cells.add(tuple(i))
+    assert (1249978, 2, 2) in cells
+    g = mdl.shape_descriptors(cp, k, h)
+    assert g["cells_inside"] == len(cells)
