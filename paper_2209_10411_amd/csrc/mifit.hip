@@ -73,8 +73,8 @@ __device__ __forceinline__ double mb_value_rcp(const double *sM, int n, double h
 // denominator: a reciprocal (four issue slots, and four of refinement) for
 // four quotients, and a control point read from LDS once for NP points.  The
 // products stay far inside the range of FP64 while coordinates are below
-// TAME_X and weights below TAME_K (r^2 < 1e33, four of them < 1e132); tame says
-// whether the model is (block-uniform).  A point that is not, or that lies so
+// TAME_X and weights below TAME_K (r^2 <= 1.2e33, four of them <= 2.1e132); tame
+// says whether the model is (wave-uniform).  A point that is not, or that lies so
 // near a control point that the denominator falls below 1e-200, is summed
 // term by term.
 constexpr double TAME_X = 1e16, TAME_K = 1e60;
@@ -107,7 +107,7 @@ __device__ __forceinline__ void mb_values(const double *sM, int n, bool tame, co
     for (int q = 0; q < NP; ++q)
         if (bad[q]) f[q] = mb_value_rcp(sM, n, hx[q], hy[q], hz[q]);
 }
-// Whether this thread's share of the model (4 n values) stays in that range.
+// Whether value t of the model's 4 n stays in that range.
 __device__ __forceinline__ bool tame_value(int t, double v) { return fabs(v) < ((t & 3) == 0 ? TAME_K : TAME_X); }
 
 // The per-point term of Eq. GSloss and its slope.
@@ -124,34 +124,61 @@ __device__ __forceinline__ double gs_slope(double f) {
 }
 
 // ------------------------------------------------------------- evaluation
-// Sum over the hull points of chunk c of (f - 1)^2 for the model in LDS: FP
-// points per lane at a time.  Whole block; every thread returns the sum.
+// Adds (f - 1)^2 at the NP hull points i, i + BLK, ... of a lane to s.
+template <int NP>
+__device__ __forceinline__ void fitness_points(const double *__restrict__ hull, long long i, long long i1,
+                                               const double *sM, int n, bool tame, double &s) {
+    double hx[NP], hy[NP], hz[NP], f[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {  // past the end: the chunk's last point, unused
+        const long long k = i + q * BLK < i1 ? i + q * BLK : i1 - 1;
+        hx[q] = hull[3 * k];
+        hy[q] = hull[3 * k + 1];
+        hz[q] = hull[3 * k + 2];
+    }
+    mb_values<NP>(sM, n, tame, hx, hy, hz, f);
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+        if (i + q * BLK < i1) {
+            const double e = f[q] - 1.0;
+            s += e * e;
+        }
+}
+
+// Sum over the hull points of chunk c of (f - 1)^2 for the model in LDS: up to
+// FP points per lane at a time, FP = 0: one, with a reciprocal per quotient.
+// Whole block; every thread returns the sum.
 // Bound by vector issue: 11.4 instructions per (hull point, control point) with
 // the shared reciprocals, 15 with one each (2400 models of 25 points on 4096:
-// 117 -> 90 us a call; two points a lane take the same time).
+// 117 -> 90 us a call; two points a lane take the same time).  A wave goes
+// through the rounds of 256 points that reach it and no others, four, two or
+// one at a time: padded to four, hulls that are no multiple of 1024 points took
+// longer than with a reciprocal each (2400 models of 25 points on 600: 23.9 us, padded 27.6, now 20.1).
 template <int FP>
 __device__ __forceinline__ double fitness_chunk(const double *__restrict__ hull, long long m, const double *sM, int n,
-                                                bool tame, int c, double *red) {
+                                                int c, double *red) {
     const long long i0 = (long long)c * CHUNK;
     const long long i1 = i0 + CHUNK < m ? i0 + CHUNK : m;
     double s = 0.0;
-    for (long long i = i0 + threadIdx.x; i < i1; i += FP * BLK) {
-        double hx[FP], hy[FP], hz[FP], f[FP];
-#pragma unroll
-        for (int q = 0; q < FP; ++q) {  // past the end: the first point again, unused
-            const long long k = i + q * BLK < i1 ? i + q * BLK : i;
-            hx[q] = hull[3 * k];
-            hy[q] = hull[3 * k + 1];
-            hz[q] = hull[3 * k + 2];
+    long long i = i0 + threadIdx.x;
+    if (FP == 0) {
+        for (; i < i1; i += BLK) {
+            const double e = mb_value_rcp(sM, n, hull[3 * i], hull[3 * i + 1], hull[3 * i + 2]) - 1.0;
+            s += e * e;
         }
-        mb_values<FP>(sM, n, tame, hx, hy, hz, f);
-#pragma unroll
-        for (int q = 0; q < FP; ++q)
-            if (i + q * BLK < i1) {
-                const double e = f[q] - 1.0;
-                s += e * e;
-            }
+        return block_sum(s, red);
     }
+    // whether the model is tame: each wave looks at all of it
+    bool ok = true;
+    for (int t = threadIdx.x & 63; t < 4 * n; t += 64) ok = ok && tame_value(t, sM[t]);
+    const bool tame = __all(ok);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+    int rounds = (int)((i1 - i0 - wave + BLK - 1) / BLK);  // wave-uniform; i1 - i0 >= 1: not below 0
+    if (FP >= 4)
+        for (; rounds >= 4; rounds -= 4, i += 4 * BLK) fitness_points<4>(hull, i, i1, sM, n, tame, s);
+    if (FP >= 2)
+        for (; rounds >= 2; rounds -= 2, i += 2 * BLK) fitness_points<2>(hull, i, i1, sM, n, tame, s);
+    for (; rounds >= 1; --rounds, i += BLK) fitness_points<1>(hull, i, i1, sM, n, tame, s);
     return block_sum(s, red);
 }
 
@@ -164,13 +191,9 @@ __global__ __launch_bounds__(BLK) void k_fitness(const double *__restrict__ hull
     __shared__ double red[4];
     const int p = blockIdx.x / nch, c = blockIdx.x - p * nch;
     const double *M = pop + (size_t)p * n * 4;
-    bool tame = true;
-    for (int t = threadIdx.x; t < 4 * n; t += BLK) {  // 4 n <= BLK: one value per thread
-        sM[t] = M[t];
-        tame = tame_value(t, M[t]);
-    }
-    tame = __syncthreads_and(tame);
-    const double s = fitness_chunk<FP>(hull, m, sM, n, tame, c, red);
+    for (int t = threadIdx.x; t < 4 * n; t += BLK) sM[t] = M[t];
+    __syncthreads();
+    const double s = fitness_chunk<FP>(hull, m, sM, n, c, red);
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
@@ -201,7 +224,6 @@ __global__ __launch_bounds__(BLK) void k_breed(const double *__restrict__ hull, 
     __shared__ double sM[MI_MAXCP * 4];
     __shared__ double red[4];
     const int a = blockIdx.x / nch, c = blockIdx.x - a * nch, g4 = 4 * n, t = threadIdx.x;
-    bool tame = true;
     if (t < g4) {  // g4 <= BLK
         double v;
         if (a < N) {
@@ -225,10 +247,9 @@ __global__ __launch_bounds__(BLK) void k_breed(const double *__restrict__ hull, 
         }
         sM[t] = v;
         if (c == 0) pool[(size_t)(N + a) * g4 + t] = v;
-        tame = tame_value(t, v);
     }
-    tame = __syncthreads_and(tame);
-    const double s = fitness_chunk<FP>(hull, m, sM, n, tame, c, red);
+    __syncthreads();
+    const double s = fitness_chunk<FP>(hull, m, sM, n, c, red);
     if (t == 0) out[blockIdx.x] = s;
 }
 
@@ -435,11 +456,24 @@ inline int chunks(long long m) { return cdiv(m, CHUNK); }
 
 lbm_status launched() { return hipGetLastError() == hipSuccess ? LBM_OK : LBM_E_HIP; }
 
-// Points per lane at a time: as many as the hull gives a lane of one block, up
-// to four (more registers, fewer waves); fewer would be repeated points.
-template <class L1, class L2, class L4>
-void by_points(long long m, L1 one, L2 two, L4 four) {
-    if (m <= BLK) one();
+// The fitness's form.  A reciprocal per quotient while the model has too few
+// control points, or the hull too few points beside them, for shared ones to
+// make up for their checks (the start of a block, and what is added per
+// point).  Time with a reciprocal each over time with shared ones, by control
+// points and hull points:
+//             40    250    500   1024   2048   4096
+//    2      0.85   0.88   0.88   0.90   0.91   0.92
+//    4      0.89   0.95   0.97   0.97   1.02   1.02
+//    6      0.87   0.95   0.97   1.01   1.05   1.06
+//    8      0.89   0.99   1.05   1.08   1.11   1.13
+//   12      0.92   1.03   1.13   1.13   1.18   1.18
+//   25      0.91   1.12   1.17   1.21   1.25   1.25
+// Shared, the points per lane at a time are as many as the hull gives a lane of
+// one block, up to four (more registers, fewer waves).
+template <class L0, class L1, class L2, class L4>
+void by_form(long long m, int n, L0 each, L1 one, L2 two, L4 four) {
+    if (n < 8 ? n < 4 || m < 2048 : n * m < 3500) each();
+    else if (m <= BLK) one();
     else if (m <= 2 * BLK) two();
     else four();
 }
@@ -449,8 +483,9 @@ lbm_status fitness_launch(const double *hull, long long m, const double *pop, in
                           hipStream_t s) {
     const int nch = chunks(m);
     double *out = nch == 1 ? F : part;
-    by_points(
-        m, [&] { k_fitness<1><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
+    by_form(
+        m, n, [&] { k_fitness<0><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
+        [&] { k_fitness<1><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
         [&] { k_fitness<2><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); },
         [&] { k_fitness<4><<<P * nch, BLK, 0, s>>>(hull, m, pop, n, nch, out); });
     if (nch > 1) k_fitness_sum<<<cdiv(P, 256), 256, 0, s>>>(part, P, nch, F);
@@ -525,7 +560,7 @@ lbm_status mi_ga(const double *hull, int64_t m, int32_t N_I, int32_t n, int32_t 
         auto breed = [&](auto kernel) {
             kernel<<<2 * N_I * nch, BLK, 0, s>>>(hull, m, A, Ue, Ze, pe, N_I, n, c, C_m, sigma_x, sigma_k, nch, sums);
         };
-        by_points(m, [&] { breed(k_breed<1>); }, [&] { breed(k_breed<2>); }, [&] { breed(k_breed<4>); });
+        by_form(m, n, [&] { breed(k_breed<0>); }, [&] { breed(k_breed<1>); }, [&] { breed(k_breed<2>); }, [&] { breed(k_breed<4>); });
         const bool fold = nch <= SEL_CHUNKS;
         if (!fold) k_fitness_sum<<<cdiv(2 * N_I, 256), 256, 0, s>>>(part, 2 * N_I, nch, FA + N_I);
         k_select<<<cdiv(3 * N_I, SEL_PER), BLK, 0, s>>>(A, FA, fold ? N_I : 3 * N_I, sums, nch, 3 * N_I, N_I, n, B, FB);

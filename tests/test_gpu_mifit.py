@@ -180,3 +180,16 @@ def test_gs_block_forms(mdl, n, m):
     Mo, Lo = mifit.gs(M0[0], H, pl, 10, 1e-5)
     assert np.abs(Mg[0] - Mo).max() <= 1e-8 * np.abs(Mo).max()
     assert np.allclose(Lg[0], Lo, rtol=1e-8, atol=0)
+
+
+@pytest.mark.parametrize("n,m", [(3, 2048), (4, 2047), (4, 2048), (7, 5000), (8, 437), (8, 438), (12, 292), (25, 600),
+                                 (25, 769), (25, 1025), (9, 2049), (64, 47), (10, 2048 + 257)])
+def test_fitness_forms(mdl, n, m):
+    """A reciprocal per quotient and shared ones, on both sides of each line
+    between them, and hulls whose last rounds of 256 points reach some waves
+    only (the bound of the tests above)."""
+    H, pl, _ = body(93, m=m)
+    pop = workloads.mi_population(H, pl, 6, n, seed=94)
+    Fg = mdl.mi_fitness(H, pop)
+    Fo = np.array([mifit.fitness(p, H) for p in pop])
+    assert np.all(np.abs(Fg - Fo) <= 1e-12 * np.abs(Fo))
