@@ -17,6 +17,7 @@ namespace {
 
 constexpr int BLK = 256;         // threads of the fitness blocks (4 waves)
 constexpr int GS_BLK = 1024;     // threads of a gradient-search block (16 waves)
+constexpr int GS_SMALL = 192;    // hull points up to which many models take blocks of 256 (mi_gs)
 constexpr int CHUNK = 2048;      // hull points per fitness block
 constexpr int SEL_MAX = 4096;    // pool size the selection holds in LDS
 constexpr int SEL_CHUNKS = 4;    // hull chunks whose sums the selection adds itself (each block for the whole pool)
@@ -320,12 +321,20 @@ __device__ __forceinline__ double gs_value(const double *sM, int n, double hx, d
     return ok && fabs(f) < 1e200 ? f : mb_value(sM, n, hx, hy, hz);
 }
 
+// Chunks of points in pass 2: as many as 1024 threads take, of four points or
+// more (two pairs over a reciprocal each).
+__host__ __device__ __forceinline__ int gs_chunks(int m, int n) {
+    const int most = GS_BLK / n, fours = (m + 3) / 4;
+    return most < fours ? most : fours;
+}
+
 // Sum over the hull points of the Eq. GSloss terms for the model in LDS.
+template <int NT>
 __device__ double gs_loss_block(const double *__restrict__ hull, long long m, const double *sM, int n, double *red) {
     double s = 0.0;
-    for (long long i = threadIdx.x; i < m; i += GS_BLK)
+    for (long long i = threadIdx.x; i < m; i += NT)
         s += gs_term(mb_value(sM, n, hull[3 * i], hull[3 * i + 1], hull[3 * i + 2]));
-    return block_sum<GS_BLK / 64>(s, red);
+    return block_sum<NT / 64>(s, red);
 }
 
 // One workgroup per model: E descent steps, cleaning, E steps.  Per step:
@@ -340,31 +349,38 @@ __device__ double gs_loss_block(const double *__restrict__ hull, long long m, co
 // slopes (32 bytes a point) instead of being read again from the caches every
 // step.  64 models of 900 to 1500 points, 25 control points: 13.5 us a step, 40
 // with four waves, exact quotients and the hull in memory.
-template <bool STAGED>
-__global__ __launch_bounds__(GS_BLK) void k_gs(const double *__restrict__ hulls, const int64_t *__restrict__ hoff,
-                                               const double *__restrict__ planes, const int64_t *__restrict__ poff,
-                                               int n, int E, double eta, double *__restrict__ Mall,
-                                               double *__restrict__ loss) {
+// Two more forms for more models than compute units, with the same chunks and
+// sums, bit for bit (mi_gs chooses): WPE = 8 holds the block to 64 registers a
+// lane, so that two share a compute unit; NT = 256 (hulls of up to 192 points,
+// which leave most of 1024 threads idle) lets several, a thread standing for
+// four of the 1024 in pass 2.
+template <bool STAGED, int NT, int WPE>
+__global__ __launch_bounds__(NT, WPE) void k_gs(const double *__restrict__ hulls, const int64_t *__restrict__ hoff,
+                                                const double *__restrict__ planes, const int64_t *__restrict__ poff,
+                                                int n, int E, double eta, double *__restrict__ Mall,
+                                                double *__restrict__ loss) {
     __shared__ double sM[MI_MAXCP * 4];
-    __shared__ double part[GS_BLK * 4];
-    __shared__ double red[GS_BLK / 64];
+    __shared__ double red[NT / 64];
     extern __shared__ double pts[];  // STAGED: x, y, z and the slope of each point; else the slopes alone
     const int b = blockIdx.x, t = threadIdx.x;
     const long long h0 = hoff[b];
-    const int m = (int)(hoff[b + 1] - h0);  // at most MI_GS_MAXPTS
+    const int m = (int)(hoff[b + 1] - h0);  // at most MI_GS_MAXPTS; with NT = 256, at most 256
     const double *hull = hulls + 3 * h0;
     double *M = Mall + (size_t)b * n * 4;
-    if (t < 4 * n) sM[t] = M[t];
+    if (t < 4 * n) sM[t] = M[t];  // 4 n <= 256
     if (STAGED)
-        for (int i = t; i < m; i += GS_BLK)
+        for (int i = t; i < m; i += NT)
             for (int a = 0; a < 3; ++a) pts[4 * i + a] = hull[3 * i + a];
     __syncthreads();
-    double L = gs_loss_block(hull, m, sM, n, red);
+    double L = gs_loss_block<NT>(hull, m, sM, n, red);
     if (t == 0) loss[3 * b] = L;
-    const int nch = GS_BLK / n;  // chunks of points in pass 2
-    const int j = t % n, c = t / n;
-    const int LP = n <= 32 ? 8 : 4;  // lanes per gene in the last sum
+    const int nch = gs_chunks(m, n);
+    const int lp = n <= 32 ? 3 : 2;  // 2^lp lanes per gene in the last sum
+    const int j0 = t % n, c0 = t / n, dj = NT % n, dc = NT / n;  // control point and chunk, and their steps
     constexpr int W = STAGED ? 4 : 1;
+    constexpr bool FIXED = NT == GS_BLK;  // a place of its own for the sums; else behind the points
+    __shared__ double fixed[FIXED ? GS_BLK * 4 : 1];
+    double *part = FIXED ? fixed : pts + W * m;
     auto point = [&](int i, double &x, double &y, double &z) {
         const double *h = STAGED ? pts + 4 * i : hull + 3 * (size_t)i;
         x = h[0];
@@ -373,15 +389,15 @@ __global__ __launch_bounds__(GS_BLK) void k_gs(const double *__restrict__ hulls,
     };
     for (int phase = 0; phase < 2; ++phase) {
         for (int it = 0; it < E; ++it) {
-            for (int i = t; i < m; i += GS_BLK) {
+            for (int i = t; i < m; i += NT) {
                 double x, y, z;
                 point(i, x, y, z);
                 pts[W * i + W - 1] = gs_slope(gs_value(sM, n, x, y, z));
             }
             __syncthreads();
-            double gk = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
-            if (c < nch) {
+            for (int v = t, j = j0, c = c0; v < nch * n; v += NT) {  // control point j, chunk c; v = c n + j
                 const double k2 = 2.0 * sM[4 * j], px = sM[4 * j + 1], py = sM[4 * j + 2], pz = sM[4 * j + 3];
+                double gk = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
                 auto add = [&](double dx, double dy, double dz, double y, double gi) {
                     const double gy_ = gi * y, w = k2 * gy_ * y;
                     gk += gy_;
@@ -412,22 +428,29 @@ __global__ __launch_bounds__(GS_BLK) void k_gs(const double *__restrict__ hulls,
                     ax -= px; ay -= py; az -= pz;
                     add(ax, ay, az, 1.0 / fma(ax, ax, fma(ay, ay, az * az)), pts[W * i + W - 1]);
                 }
+                part[4 * v] = gk; part[4 * v + 1] = gx;
+                part[4 * v + 2] = gy; part[4 * v + 3] = gz;
+                if (FIXED) break;  // one round
+                j += dj;
+                c += dc;
+                if (j >= n) {
+                    j -= n;
+                    ++c;
+                }
             }
-            part[4 * t] = gk; part[4 * t + 1] = gx;
-            part[4 * t + 2] = gy; part[4 * t + 3] = gz;
             __syncthreads();
-            {  // gene o of control point o / 4: LP partial sums, then a butterfly
-                const int o = t / LP, l = t % LP;
+            for (int v = t; v < 4 * n << lp; v += NT) {  // gene o: 2^lp partial sums, then a butterfly
+                const int o = v >> lp, l = v - (o << lp);
                 double G = 0.0;
-                if (o < 4 * n)
-                    for (int cc = l; cc < nch; cc += LP) G += part[4 * cc * n + o];
-                for (int d = LP / 2; d > 0; d >>= 1) G += __shfl_xor(G, d);
-                if (o < 4 * n && l == 0) sM[o] -= eta * G;
+                for (int cc = l; cc < nch; cc += 1 << lp) G += part[4 * cc * n + o];
+                for (int d = 1 << (lp - 1); d > 0; d >>= 1) G += __shfl_xor(G, d);
+                if (l == 0) sM[o] -= eta * G;
+                if (FIXED) break;
             }
             __syncthreads();
         }
         if (phase == 0) {
-            L = gs_loss_block(hull, m, sM, n, red);
+            L = gs_loss_block<NT>(hull, m, sM, n, red);
             if (t == 0) loss[3 * b + 1] = L;
             // anomaly cleaning: negative weights and control points outside the hull
             if (t < n) {
@@ -440,15 +463,16 @@ __global__ __launch_bounds__(GS_BLK) void k_gs(const double *__restrict__ hulls,
             __syncthreads();
         }
     }
-    L = gs_loss_block(hull, m, sM, n, red);
+    L = gs_loss_block<NT>(hull, m, sM, n, red);
     if (t == 0) loss[3 * b + 2] = L;
     if (t < 4 * n) M[t] = sM[t];
 }
 
 // Hulls of up to GS_STAGED points are kept in LDS (96 KB beside the 34 KB of
-// the sums, of the 160 KB of a compute unit); a larger one leaves its points in
+// the model and the sums, of the 160 KB of a compute unit); a larger one leaves its points in
 // memory.
 constexpr int GS_STAGED = 3072;
+constexpr int GS_PAIR = 1400;  // two blocks share the 160 KB
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -602,14 +626,31 @@ lbm_status mi_gs(const double *hulls, const int64_t *hull_off, const double *pla
     // Beyond 64 KB of LDS a kernel asks for it, and the request belongs to the
     // kernel, not to the launch: it is each form's largest (130 and 82 KB with
     // the static 34) in every call, so that calls on several threads agree.
-    auto run = [&](auto kernel, int max_lds, size_t lds) {
+    const size_t points = (staged ? 32 : 8) * (size_t)most;
+    auto run = [&](auto kernel, int threads, int max_lds, size_t lds) {
         if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds) != hipSuccess)
             return LBM_E_HIP;
-        kernel<<<B, GS_BLK, lds, s>>>(hulls, hull_off, planes, plane_off, n, E, eta, M, loss);
+        kernel<<<B, threads, lds, s>>>(hulls, hull_off, planes, plane_off, n, E, eta, M, loss);
         return launched();
     };
-    return staged ? run(k_gs<true>, 32 * GS_STAGED, 32 * (size_t)most)
-                  : run(k_gs<false>, 8 * MI_GS_MAXPTS, 8 * (size_t)most);
+    constexpr int MAX_STAGED = 32 * GS_STAGED, MAX_SMALL = 32 * GS_SMALL + 32 * GS_BLK, MAX_SLOPES = 8 * MI_GS_MAXPTS;
+    // Up to one model a compute unit: the form without a register limit.  More:
+    // two blocks a unit where their LDS allows it; beyond two a unit and with
+    // small hulls, blocks of 256.  Us a call of 20 steps with the form taken and
+    // with the first one:
+    //   models   25 control points on 100   300   500       10 on 100
+    //     300        143 / 176        199 / 235   250 / 282   103 / 135
+    //     512        148 / 180        210 / 242   263 / 288   105 / 136
+    //    1024        214 / 306                                130 / 223
+    int dev = 0, cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return LBM_E_HIP;
+    if (!staged) return run(k_gs<false, GS_BLK, 1>, GS_BLK, MAX_SLOPES, points);
+    if (B > 2 * cu && most <= GS_SMALL)
+        return run(k_gs<true, 256, 1>, 256, MAX_SMALL, points + 32 * (size_t)n * gs_chunks((int)most, n));
+    if (B > cu && most <= GS_PAIR) return run(k_gs<true, GS_BLK, 8>, GS_BLK, MAX_STAGED, points);
+    return run(k_gs<true, GS_BLK, 1>, GS_BLK, MAX_STAGED, points);
 }
 
 // ---------------------------------------------- fitness without allocation

@@ -22,6 +22,14 @@ int hipMemcpyAsync(void *dst, const void *src, size_t n, int, void *) {
 }
 int hipStreamSynchronize(void *) { return 0; }
 int hipGetLastError() { return 0; }
+int hipGetDevice(int *dev) {
+    *dev = 0;
+    return 0;
+}
+int hipDeviceGetAttribute(int *value, int, int) {
+    *value = 256;  // the one that is asked for: compute units
+    return 0;
+}
 int hipFuncSetAttribute(const void *f, int attr, int value) {
     printf("limit %p %d %d\n", f, attr, value);
     return 0;

@@ -193,3 +193,20 @@ def test_fitness_forms(mdl, n, m):
     Fg = mdl.mi_fitness(H, pop)
     Fo = np.array([mifit.fitness(p, H) for p in pop])
     assert np.all(np.abs(Fg - Fo) <= 1e-12 * np.abs(Fo))
+
+
+@pytest.mark.parametrize("n,m", [(1, 5), (6, 60), (10, 192), (33, 192), (25, 193), (64, 190), (7, 1400), (7, 1401)])
+def test_gs_of_many_models(mdl, n, m):
+    """A model's result does not depend on how many others are searched with
+    it: alone, among 300 (two blocks a compute unit) and among 600 (small hulls
+    in blocks of 256), bit for bit; and the oracle's."""
+    H, pl, truth = body(97, n_cp=4, R=6.0, m=max(m, 40))
+    H = H[:m]
+    M0 = workloads.mi_population(H, pl, 1, n, seed=98)
+    one, Lone = mdl.mi_gs([H], [pl], M0, 3, 1e-6)
+    Mo, Lo = mifit.gs(M0[0], H, pl, 3, 1e-6)
+    assert np.abs(one[0] - Mo).max() <= 1e-8 * np.abs(Mo).max()
+    assert np.allclose(Lone[0], Lo, rtol=1e-8, atol=0)
+    for B in (300, 600):
+        M, L = mdl.mi_gs([H] * B, [pl] * B, np.repeat(M0, B, axis=0), 3, 1e-6)
+        assert np.array_equal(M, np.repeat(one, B, axis=0)) and np.array_equal(L, np.repeat(Lone, B, axis=0))
