@@ -1638,7 +1638,7 @@ lbm_status write_table(lbm_batch *b) {
     b->any_rigid = b->any_warm = false;
     long long links = 0;  // the solver's form follows the links of the whole launch
     for (int i = 0; i < b->n; ++i) links += link_q_expected(b->cs[i]->p);
-    b->link_q_one = link_q_one(links);
+    b->link_q_one = link_q_one(links, BESIDE_BATCH);
     for (int i = 0; i < b->n; ++i) {
         case_blocks(b->cs[i], b->link_q_one, &nb[(size_t)i * BK_N]);
         for (int k = 0; k < BK_N; ++k) tot[k] += nb[(size_t)i * BK_N + k];

@@ -2386,8 +2386,7 @@ __global__ __launch_bounds__(256) void k_link_emit_tiles(Params p, RegionMap rm,
 // are bound by vector issue once they fill the chip.  1.45 M links (200 bodies
 // in 256^3): G = 8 354 us alone and 577 us beside the stream-collide, G = 1
 // 188 and 270 us; 24 systems, 200 k links in one launch, 204 -> 76 us; 900
-// links: G = 8 14 us, G = 1 21 us.  The lines cross where G = 8's waves (one
-// per eight links) begin to queue.
+// links: G = 8 14 us, G = 1 21 us.  link_q_one draws the line.
 constexpr int NR_WARM_MAX = 30, NR_MAX = 100;
 // Warm start, first pass: the network's q for every link of the list, written
 // to l_q as the solver's start (one wave per 32 links, the wave inference of
@@ -2683,10 +2682,21 @@ constexpr int MARK_COLUMNS = 2048;
 static int expected_links(const Params &p) { return p.est_links > 0 ? min(p.est_links, p.link_cap) : p.link_cap; }
 // a multiple of the XCDs: each takes its share of the list
 int link_grid(const Params &p) { return N_XCD * max(1, min(cdiv(expected_links(p), 256 * N_XCD), 1024)); }
-// G = 8 below LINKQ_ONE links: 4096 waves of eight links are four per SIMD, as
-// many as are resident; beyond, they run in rounds and G = 1 is the shorter.
-constexpr int LINKQ_ONE = 32768;
-bool link_q_one(long long links) { return links >= LINKQ_ONE; }
+// Expected links (half as many again as there are, and 1024) from which the
+// solver takes G = 1.  Beside a stream-collide of few blocks a CU, G = 8's
+// waves go through four rounds of the resident 4096 before G = 1, whose chain is
+// eight times as long, is the shorter; the fuller the CUs, the sooner.  Step in
+// us, G = 8 / G = 1:
+//   two or three blocks a CU, or FP32   33 k links, 96^3: 113 / 130, 73 k: 182 / 188;
+//                                       89 k, 128^3: 174 / 181, 177 k: 325 / 304;
+//                                       51 k, 224^3, five blocks: 307 / 309
+//   16-bit storage, four or more        33 k, 160^3: 132 / 129; 51 k, 224^3: 208 / 188;
+//                                       70 k, 256^3: 270 / 267
+//   a batch (seven)                     52 k, 30 systems, BF16: 233 / 224; 93 k, 24 systems,
+//                                       FP32: 965 / 975; 404 k: 569 (six blocks) / 494
+bool link_q_one(long long links, LinkqBeside beside) {
+    return links >= (beside == BESIDE_BATCH ? 32768 : beside == BESIDE_16_BIT ? 65536 : 150000);
+}
 int link_q_grid(const Params &p, bool one) {
     return max(1, min(cdiv(expected_links(p), one ? 256 : 32), NR_BLOCKS));
 }
@@ -2802,7 +2812,8 @@ static void launch_step_kernels_t(const StepArgs &a) {
             k_link_emit_tiles<<<emit_grid(p), 256, 0, a.stream>>>(p, a.rm, a.P, a.lmask, a.blk_cnt, a.body_stats,
                                                                      a.part_first_blk, a.l_off, a.l_node, a.l_do,
                                                                      a.cnt);
-            const bool one = link_q_one(link_q_expected(p));
+            const bool one =
+                link_q_one(link_q_expected(p), p.storage != 0 && a.bulk_blocks >= 4 ? BESIDE_16_BIT : BESIDE_FEW);
             const int qg = link_q_grid(p, one);
             auto solve = [&](auto kernel, const _Float16 *w) {
                 kernel<<<qg, 256, 0, a.stream>>>(p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, w);

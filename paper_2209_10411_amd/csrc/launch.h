@@ -73,8 +73,11 @@ void launch_case_batch(int storage, BatchOp op, const CaseArgs *cs, const int *m
 // a system in the batched launches).
 int link_grid(const Params &p);
 // The link solver takes one lane per link (else eight) from a number of links
-// on; its grid for a system under either form.
-bool link_q_one(long long links);
+// on, by what runs beside it (a stream-collide of 16-bit storage with four
+// blocks a CU or more, a batch's, or any other); its grid for a system under
+// either form.
+enum LinkqBeside { BESIDE_FEW, BESIDE_16_BIT, BESIDE_BATCH };
+bool link_q_one(long long links, LinkqBeside beside);
 long long link_q_expected(const Params &p);
 int link_q_grid(const Params &p, bool one);
 

@@ -208,3 +208,47 @@ def test_room_left_to_the_boundary_chain_changes_no_bit(mdl, size, storage):
         assert np.array_equal(sim.particles()[0][key], ens.cases[0].particles()[0][key])
     ens.close()
     sim.close()
+
+
+def test_link_solver_forms_of_one_system(mdl):
+    """A suspension of some 60 k links: alone the solver takes eight lanes per
+    link (below 150 000 expected links), in a batch one.  Same links, fields and
+    bodies."""
+    cfg = workloads.config5(8, 128, seed=6)
+    cfg.quad_h = 0.5
+    sim, ens = mdl.Simulation(cfg), mdl.Ensemble([cfg])
+    sim.step(4)
+    ens.step(4)
+    n = len(sim.links()[0])
+    print(f"links {n}", flush=True)
+    assert 32768 <= 3 * n // 2 + 1024 < 150000
+    assert_same(ens.cases[0], (sim.populations(), sim.owner(), sim.particles()), cfg.name)
+    for a, b in zip(sim.links(), ens.cases[0].links()):
+        assert np.array_equal(a, b)
+    ens.close()
+    sim.close()
+
+
+def test_link_solver_forms_of_16_bit_storage(mdl):
+    """Bodies of given motion in a walled box of 2.1 M nodes (two stream-collide
+    blocks a CU, eight lanes per link) and, at the same places, in one of 5.5 M
+    (four blocks, one lane): the same link fractions."""
+    found = []
+    for L in (128, 176):
+        cfg = workloads.config5(8, 128, seed=6)
+        cfg.nx = cfg.ny = cfg.nz = L
+        cfg.periodic, cfg.counter_force, cfg.contact_kn, cfg.quad_h = 0, 0, 0.0, 0.5
+        cfg.storage = workloads.STORE_BF16
+        for i, p in enumerate(cfg.particles):
+            p.x = np.array([33.0 + 62.0 * (i >> a & 1) + 0.37 * i for a in range(3)])
+            p.mode = workloads.MODE_KINEMATIC
+            p.v, p.omega = np.array([0.003, -0.002, 0.001 * i]), np.array([0.001, 0.002, -0.001])
+            assert p.bounding_radius() < 31.0
+        sim = mdl.Simulation(cfg)
+        sim.step(3)
+        node, d, owner, q = sim.links()
+        assert 65536 <= 3 * len(q) // 2 + 1024 < 150000
+        found.append((node % L, node // L % L, node // (L * L), d, owner, q))
+        sim.close()
+    for a, b in zip(*found):
+        assert np.array_equal(a, b)
