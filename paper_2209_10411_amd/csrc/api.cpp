@@ -446,13 +446,18 @@ lbm_status check_device(lbm_ctx *c) {
 //                                   8.2 M: 210 -> 208 (four: 212); 16.4 M, two bodies: 421 -> 412 (417)
 //   16 bit two up to 2.9 M          1.77 M: 66 -> 64; 2.81 M: 74 -> 69; 2.76 M, two bodies: 98 -> 88
 //          above, four              4.19 M: 79 (two: 101, six: 90); 16.4 M, two bodies: 226 (254)
-//          five from 7.5 M nodes without contact  8.2 M: 120 -> 116; 16.8 M: 243 -> 239
-// Many cut links (more than one for 50 nodes) make the chain the longer one at
-// any size: two (256^3, 200 bodies, 1.45 M links: 1.52 against 1.64 ms with six).
+//          five from 7.5 M nodes without contact and with few cut links (less than
+//          one for 400 nodes): 8.2 M: 120 -> 116; 16.8 M: 243 -> 239; five bodies in
+//          16.8 M: 254 -> 253; but six in 8 M, one for 189: four 136, five 176
+// Many cut links make the chain the longer one: two from one for 50 nodes on
+// (six bodies in 2.1 M, FP32: three 107 -> 98; forty in 11.2 M, 16 bit: four 352
+// -> 328), in FP32 above 2.6 M nodes, where two blocks lose the stream-collide
+// more than the chain gains, from one for 15 on (sixty bodies in 16.8 M, one for
+// 39: two 692, four 595; 200, one for 11: two 1081, four 1085).
 int bulk_blocks_beside_chain(const Params &p, long long n_links) {
     const double m = (double)p.N / 1e6;
-    if (50 * n_links > (long long)p.N) return 2;
-    if (p.storage != 0) return m <= 2.9 ? 2 : m < 7.5 || p.contact ? 4 : 5;
+    if ((p.storage == 0 && m > 2.6 ? 15 : 50) * n_links > (long long)p.N) return 2;
+    if (p.storage != 0) return m <= 2.9 ? 2 : m < 7.5 || p.contact || 400 * n_links > (long long)p.N ? 4 : 5;
     return m <= 1.6 ? 2 : m <= 2.6 ? 3 : m > 5.0 && p.nx % 64 != 0 ? 5 : 4;
 }
 

@@ -2690,12 +2690,12 @@ int link_grid(const Params &p) { return N_XCD * max(1, min(cdiv(expected_links(p
 //   two or three blocks a CU, or FP32   33 k links, 96^3: 113 / 130, 73 k: 182 / 188;
 //                                       89 k, 128^3: 174 / 181, 177 k: 325 / 304;
 //                                       51 k, 224^3, five blocks: 307 / 309
-//   16-bit storage, four or more        33 k, 160^3: 132 / 129; 51 k, 224^3: 208 / 188;
+//   16-bit storage, four or more        33 k, 224^3: 171 / 176; 42 k, 200^3: 170 / 162; 51 k, 224^3: 208 / 188;
 //                                       70 k, 256^3: 270 / 267
 //   a batch (seven)                     52 k, 30 systems, BF16: 233 / 224; 93 k, 24 systems,
 //                                       FP32: 965 / 975; 404 k: 569 (six blocks) / 494
 bool link_q_one(long long links, LinkqBeside beside) {
-    return links >= (beside == BESIDE_BATCH ? 32768 : beside == BESIDE_16_BIT ? 65536 : 150000);
+    return links >= (beside == BESIDE_BATCH ? 32768 : beside == BESIDE_16_BIT ? 57344 : 150000);
 }
 int link_q_grid(const Params &p, bool one) {
     return max(1, min(cdiv(expected_links(p), one ? 256 : 32), NR_BLOCKS));
