@@ -1539,6 +1539,7 @@ struct lbm_batch {
     std::vector<CaseArgs> h_args;
     std::vector<Params> h_p;  // each system's constants when the tables were written (byte copies)
     bool any_rigid = false, any_warm = false, link_q_one = false;
+    int bulk_blocks = 7;  // stream-collide blocks of four waves per CU
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<uintptr_t> graph_key;
@@ -1625,6 +1626,20 @@ void drop_graph(lbm_batch *b);
 
 // Writes the launch tables for the systems' current state.  A captured graph
 // holds launch sizes and table offsets of the old tables: it is dropped.
+// Stream-collide blocks (of four waves) per CU in a batch.  Seven: an ensemble's
+// stream-collide is mostly much longer than the boundary kernels beside it,
+// which want less room (24 systems, us per step with six, seven and eight: FP32
+// 992, 975, 1004, BF16 829, 770, 787; 64 systems, FP32 2466, 2428, 2396, but in
+// eighths of all their boundary kernels: 4 systems 179, 176, 221).  Five where
+// the systems are small or hold many bodies, so that the boundary kernels take
+// the longer (six, seven, five; at one cut link for so many nodes):
+//   FP32   64 of 0.2 M nodes (124): 505, 503, 475; 32 of 0.5 M (169): 573, 560, 553;
+//          4 of 0.9 M, four bodies each (33): 228, 244, 218
+//   BF16   64 of 0.2 M: 429, 437, 404; 32 of 0.5 M: 488, 458, 478
+int batch_bulk_blocks(int storage, long long nodes, long long links) {
+    return (storage == 0 ? 200 : 150) * links > nodes ? 5 : 7;
+}
+
 lbm_status write_table(lbm_batch *b) {
     drop_graph(b);
     b->h_cases.resize(b->n);
@@ -1641,9 +1656,17 @@ lbm_status write_table(lbm_batch *b) {
     std::vector<int> nb((size_t)b->n * BK_N);
     int tot[BK_N] = {};
     b->any_rigid = b->any_warm = false;
-    long long links = 0;  // the solver's form follows the links of the whole launch
-    for (int i = 0; i < b->n; ++i) links += link_q_expected(b->cs[i]->p);
-    b->link_q_one = link_q_one(links, BESIDE_BATCH);
+    // the solver's form follows the links of the whole launch, the stream-collide's
+    // blocks their number (as estimate_lists counted them) and the nodes
+    long long expected = 0, links = 0, nodes = 0;
+    for (int i = 0; i < b->n; ++i) {
+        const long long e = link_q_expected(b->cs[i]->p);
+        expected += e;
+        links += std::max(0ll, 2 * (e - 1024) / 3);
+        nodes += b->cs[i]->p.N;
+    }
+    b->bulk_blocks = batch_bulk_blocks(b->storage, nodes, links);
+    b->link_q_one = link_q_one(expected, b->bulk_blocks == 5 ? BESIDE_BATCH : BESIDE_LONG_BATCH);
     for (int i = 0; i < b->n; ++i) {
         case_blocks(b->cs[i], b->link_q_one, &nb[(size_t)i * BK_N]);
         for (int k = 0; k < BK_N; ++k) tot[k] += nb[(size_t)i * BK_N + k];
@@ -1749,7 +1772,7 @@ lbm_status enqueue_batch_step(lbm_batch *b) {
     run(OP_EMIT, BK_REGION);
     run(b->any_warm ? (b->link_q_one ? OP_LINKQ_WARM_ONE : OP_LINKQ_WARM) : b->link_q_one ? OP_LINKQ_ONE : OP_LINKQ,
         BK_LINKQ);
-    launch_bulk_batch(b->storage, b->bw, b->d_cases, b->d_blk, b->nblocks, b->phase & 1, b->main);
+    launch_bulk_batch(b->storage, b->bw, b->d_cases, b->d_blk, b->nblocks, b->phase & 1, b->bulk_blocks, b->main);
     HIPCHK(hipStreamWaitEvent(b->main, b->ev_flags[0], 0));
     for (int i = 0; i < b->n; ++i) {
         lbm_ctx *c = b->cs[i];
@@ -2043,10 +2066,10 @@ lbm_status lbm_autotune(lbm_batch *b, double budget_ms, const char *cache_path) 
     };
     auto time_launch = [&](const BulkCase *cases, const int *blk, int nblk, int bw, float &best) -> lbm_status {
         best = 1e30f;
-        launch_bulk_batch(b->storage, bw, cases, blk, nblk, 0, b->main);  // warm-up
+        launch_bulk_batch(b->storage, bw, cases, blk, nblk, 0, b->bulk_blocks, b->main);  // warm-up
         for (int r = 0; r < 3; ++r) {
             HIPCHK(hipEventRecord(e0, b->main));
-            launch_bulk_batch(b->storage, bw, cases, blk, nblk, 0, b->main);
+            launch_bulk_batch(b->storage, bw, cases, blk, nblk, 0, b->bulk_blocks, b->main);
             HIPCHK(hipEventRecord(e1, b->main));
             HIPCHK(hipEventSynchronize(e1));
             float ms = 0;

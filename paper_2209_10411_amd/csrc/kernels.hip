@@ -2692,9 +2692,13 @@ int link_grid(const Params &p) { return N_XCD * max(1, min(cdiv(expected_links(p
 //                                       51 k, 224^3, five blocks: 307 / 309
 //   16-bit storage, four or more        33 k, 224^3: 171 / 176; 42 k, 200^3: 170 / 162; 51 k, 224^3: 208 / 188;
 //                                       70 k, 256^3: 270 / 267
-//   a batch (seven)                     52 k, 30 systems, BF16: 233 / 224; 93 k, 24 systems,
-//                                       FP32: 965 / 975; 404 k: 569 (six blocks) / 494
+//   a batch of five blocks              21 k, 12 systems: 137 / 140; 111 k, 64: 484 / 479,
+//                                       BF16 414 / 403; 404 k, six: 527 / 455
+// A batch of seven blocks has a stream-collide far longer than the solver in
+// either form, and more waves in fewer lanes disturb it less (24 systems, 93 k:
+// 965 / 975; 64, 218 k: 2402 / 2428; 96, 315 k: 3437 / 3471).
 bool link_q_one(long long links, LinkqBeside beside) {
+    if (beside == BESIDE_LONG_BATCH) return false;
     return links >= (beside == BESIDE_BATCH ? 32768 : beside == BESIDE_16_BIT ? 57344 : 150000);
 }
 int link_q_grid(const Params &p, bool one) {
@@ -2849,21 +2853,17 @@ void launch_fill_u8(uint8_t *a, long long n, uint8_t v, hipStream_t s) {
 }
 template <int S>
 static void launch_bulk_batch_t(int bw, const BulkCase *cases, const int *blk_case, int nblocks, int parity,
-                                hipStream_t s) {
+                                int blocks, hipStream_t s) {
     if (nblocks <= 0) return;
-    // Seven blocks of four waves per CU: an ensemble's stream-collide is much longer
-    // than the boundary kernels beside it, which want less room (24 systems, us
-    // per step with six, seven and eight: FP32 985, 970, 1001, BF16 824, 764, 782;
-    // 64 systems, FP32: 2460, 2431, 2365)
-    if (bw == 4) k_bulk_batch<S, 4><<<nblocks, 256, bulk_lds_reserve(4, 7), s>>>(cases, blk_case, parity);
+    if (bw == 4) k_bulk_batch<S, 4><<<nblocks, 256, bulk_lds_reserve(4, blocks), s>>>(cases, blk_case, parity);
     else k_bulk_batch<S, 8><<<nblocks, 512, bulk_lds_reserve(8), s>>>(cases, blk_case, parity);
 }
 
 void launch_bulk_batch(int storage, int bw, const BulkCase *cases, const int *blk_case, int nblocks, int parity,
-                       hipStream_t s) {
-    if (storage == 1) launch_bulk_batch_t<1>(bw, cases, blk_case, nblocks, parity, s);
-    else if (storage == 2) launch_bulk_batch_t<2>(bw, cases, blk_case, nblocks, parity, s);
-    else launch_bulk_batch_t<0>(bw, cases, blk_case, nblocks, parity, s);
+                       int blocks, hipStream_t s) {
+    if (storage == 1) launch_bulk_batch_t<1>(bw, cases, blk_case, nblocks, parity, blocks, s);
+    else if (storage == 2) launch_bulk_batch_t<2>(bw, cases, blk_case, nblocks, parity, blocks, s);
+    else launch_bulk_batch_t<0>(bw, cases, blk_case, nblocks, parity, blocks, s);
 }
 
 template <int S>

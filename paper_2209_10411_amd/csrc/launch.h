@@ -58,9 +58,10 @@ void launch_reset_counters(Counters *cnt, hipStream_t s);
 // in-place refill and counted per body.
 void launch_uncovered(const Params &p, const int32_t *own_old, const int32_t *own_new, uint32_t *special,
                       Counters *cnt, int *body_stats, hipStream_t s);
-// Batched stream-collide of an ensemble (bw: waves per block, 4 or 8).
+// Batched stream-collide of an ensemble (bw: waves per block, 4 or 8; blocks of
+// four waves allowed per CU).
 void launch_bulk_batch(int storage, int bw, const BulkCase *cases, const int *blk_case, int nblocks, int parity,
-                       hipStream_t s);
+                       int blocks, hipStream_t s);
 // fresh: the flag buffers hold flags of the current pose only (after a re-flag)
 void launch_refresh_pose(const Params &p, DevParticle *P, int fresh, hipStream_t s);
 
@@ -74,9 +75,9 @@ void launch_case_batch(int storage, BatchOp op, const CaseArgs *cs, const int *m
 int link_grid(const Params &p);
 // The link solver takes one lane per link (else eight) from a number of links
 // on, by what runs beside it (a stream-collide of 16-bit storage with four
-// blocks a CU or more, a batch's, or any other); its grid for a system under
-// either form.
-enum LinkqBeside { BESIDE_FEW, BESIDE_16_BIT, BESIDE_BATCH };
+// blocks a CU or more, a batch's of five, a batch's of seven, or any other); its
+// grid for a system under either form.
+enum LinkqBeside { BESIDE_FEW, BESIDE_16_BIT, BESIDE_BATCH, BESIDE_LONG_BATCH };
 bool link_q_one(long long links, LinkqBeside beside);
 long long link_q_expected(const Params &p);
 int link_q_grid(const Params &p, bool one);
