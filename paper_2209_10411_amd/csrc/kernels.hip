@@ -634,7 +634,7 @@ __device__ __forceinline__ float collide_lane(float d, int i, float dr, float jx
 // both populations relative to w rho0, dT = (x_w - X) x dP.  Each wave's chunk of 64 links sums its links per
 // body (a fixed butterfly) into part[chunk + body] (deterministic).
 // Block bid of nblk (a whole grid, or one system's range of a batched grid).
-template <int S>
+template <int S, bool EIGHTHS>
 __device__ __forceinline__ void links_body(const Params &p, const typename Store<S>::T *__restrict__ A,
                                            typename Store<S>::T *__restrict__ B,
                                            const int32_t *__restrict__ own,
@@ -646,10 +646,15 @@ __device__ __forceinline__ void links_body(const Params &p, const typename Store
     const int t = threadIdx.x, lane = t & 63;
     const int nl = cnt->n_links;
     const int nblock = (nl + 255) >> 8;  // 256 links per block and round, a chunk of 64 per wave
-    // each XCD takes one eighth of the list (links next to each other in it read
-    // the same lines of the populations)
-    const int eighth = (nblock + N_XCD - 1) / N_XCD, end = min(nblock, (bid % N_XCD + 1) * eighth);
-    for (int cb = bid % N_XCD * eighth + bid / N_XCD; cb < end; cb += max(1, nblk / N_XCD)) {
+    // EIGHTHS: each XCD takes one eighth of the list (links next to each other in
+    // it read the same lines of the populations; nblk a multiple of the XCDs).  In a
+    // batch the list's blocks go round the grid (24 systems 962 against 973 us a
+    // step, 64 2368 against 2412).
+    const int eighth = (nblock + N_XCD - 1) / N_XCD;
+    const int begin = EIGHTHS ? bid % N_XCD * eighth + bid / N_XCD : bid;
+    const int end = EIGHTHS ? min(nblock, (bid % N_XCD + 1) * eighth) : nblock;
+    const int step = EIGHTHS ? max(1, nblk / N_XCD) : nblk;
+    for (int cb = begin; cb < end; cb += step) {
         const int l = (cb << 8) + t, ch = l >> 6;
         double dP[3] = {0, 0, 0}, dT[3] = {0, 0, 0};
         int pi = -1;
@@ -756,7 +761,7 @@ __global__ __launch_bounds__(256) void k_links(Params p, const typename Store<S>
                                                const uint32_t *__restrict__ l_do,
                                                const double *__restrict__ l_q, double *__restrict__ part,
                                                Counters *__restrict__ cnt) {
-    links_body<S>(p, A, B, own, P, l_node, l_do, l_q, part, cnt, blockIdx.x, gridDim.x);
+    links_body<S, true>(p, A, B, own, P, l_node, l_do, l_q, part, cnt, blockIdx.x, gridDim.x);
 }
 
 // ------------------------------------------------------- rigid body (FP64)
@@ -2617,7 +2622,7 @@ template <int S>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_links_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
     using T = typename Store<S>::T;
     const CaseArgs &a = cs[map[blockIdx.x]];
-    links_body<S>(a.p, (const T *)a.A, (T *)a.B, a.own_old, a.P, a.l_node, a.l_do, a.l_q, a.part, a.cnt,
+    links_body<S, false>(a.p, (const T *)a.A, (T *)a.B, a.own_old, a.P, a.l_node, a.l_do, a.l_q, a.part, a.cnt,
                   (int)blockIdx.x - a.first[BK_LINKS], a.nblk[BK_LINKS]);
 }
 
