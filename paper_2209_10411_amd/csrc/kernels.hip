@@ -2619,7 +2619,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // system map[b] as its block b - first[kind] (the same code as the
 // one-system launches above).
 template <int S>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_links_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
+__global__ __launch_bounds__(256) void k_links_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
     using T = typename Store<S>::T;
     const CaseArgs &a = cs[map[blockIdx.x]];
     links_body<S, false>(a.p, (const T *)a.A, (T *)a.B, a.own_old, a.P, a.l_node, a.l_do, a.l_q, a.part, a.cnt,
@@ -2668,7 +2668,7 @@ __global__ __launch_bounds__(256) void k_link_guess_batch(const CaseArgs *__rest
 }
 
 template <bool WARM, int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_link_q_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
+__global__ __launch_bounds__(256) void k_link_q_batch(const CaseArgs *__restrict__ cs, const int *__restrict__ map) {
     const CaseArgs &a = cs[map[blockIdx.x]];
     link_q_body<WARM, G>(a.p, a.P, a.l_node, a.l_do, a.l_q, a.cnt, a.nrs, a.warm, (int)blockIdx.x - a.first[BK_LINKQ],
                       a.nblk[BK_LINKQ]);
