@@ -168,11 +168,11 @@ __global__ __launch_bounds__(MLP_BLK) void k_mlp_slice(const TA *__restrict__ X,
         float z[MLP_N];
         layer(x, MLP_IN, w1, MLP_H, (float)bias[u], z);
 #pragma unroll
-        for (int q = 0; q < MLP_N; ++q) h1[u][q0 + q] = q0 + q < nb ? (float)(TA)tanhf(z[q]) : 0.f;
+        for (int q = 0; q < MLP_N; ++q) h1[u][q0 + q] = (float)(TA)tanhf(z[q]);
         __syncthreads();
         layer(h1, MLP_H, w2, W2P, (float)bias[MLP_H + u], z);
 #pragma unroll
-        for (int q = 0; q < MLP_N; ++q) h2[u][q0 + q] = q0 + q < nb ? (float)(TA)tanhf(z[q]) : 0.f;
+        for (int q = 0; q < MLP_N; ++q) h2[u][q0 + q] = (float)(TA)tanhf(z[q]);
         __syncthreads();
         if (t < MLP_T * MLP_OUT) {  // outputs and the masked squared error's gradient (mean over the batch)
             const int b = t / MLP_OUT, j = t - b * MLP_OUT;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(MLP_BLK) void k_mlp_slice(const TA *__restrict__ X,
 #pragma unroll
             for (int n = 0; n < MLP_OUT; ++n) e += d3[n][q0 + q] * (float)w3[u * MLP_OUT + n];
             const float h = h2[u][q0 + q];
-            d2[u][q0 + q] = q0 + q < nb ? e * (1.f - h * h) : 0.f;
+            d2[u][q0 + q] = e * (1.f - h * h);
         }
         __syncthreads();
         {
@@ -207,13 +207,17 @@ __global__ __launch_bounds__(MLP_BLK) void k_mlp_slice(const TA *__restrict__ X,
 #pragma unroll
             for (int q = 0; q < MLP_N; ++q) {
                 const float h = h1[u][q0 + q];
-                d1[u][q0 + q] = q0 + q < nb ? e[q] * (1.f - h * h) : 0.f;
+                d1[u][q0 + q] = e[q] * (1.f - h * h);
             }
         }
+        // samples past the slice's end: nothing of them reaches the gradients,
+        // whatever the weights (one that FP16 holds as infinite makes them NaN,
+        // which zero output gradients do not undo)
+        if (nb < MLP_T)
+            for (int q = 0; q < MLP_N; ++q)
+                if (q0 + q >= nb) h1[u][q0 + q] = d1[u][q0 + q] = d2[u][q0 + q] = 0.f;
         __syncthreads();
-        // gradients: samples past the slice's end have activations and layer
-        // gradients of zero, whatever the weights (one that FP16 holds as
-        // infinite makes them NaN, which zero output gradients do not undo)
+        // gradients: samples past the slice's end are zero
         auto rows = [&](const float(*in)[MLP_TP], int K, const float(*dz)[MLP_TP], float *g, int R) {
             float dv[MLP_T];
 #pragma unroll
