@@ -25,9 +25,13 @@
  *          2 h, i < ceil(2 half / h) + 1) in the plane of the two longer axes
  *          about the centroid, with at least one sample along the shortest
  *          axis (same grid) where C >= 1.
- * One thread per grid cell (or column), block sums in FP64 to per-block slots
- * in the workspace, added on the host in block order; the 3x3 eigenproblem is
- * solved on the host (Jacobi rotations).
+ * Each grid sample is decided once, first in FP32 where its error bound leaves
+ * no doubt; integer sums of the inside cells' indices give volume, centroid and
+ * moments, FP64 block sums in per-block slots the area.  One control point, grids
+ * whose rows do not fit the workspace, and the moments of bodies with two equal
+ * principal ones take one thread per cell, with block sums in FP64 added on the
+ * host in block order; the 3x3 eigenproblem is solved on the host (Jacobi
+ * rotations).
  *
  * Memory: cp, k are host arrays (copied); work is caller-owned device memory
  * of mb_shape_work_bytes bytes.  Synchronises.  Errors: LBM_E_INVALID (NULL
